@@ -344,8 +344,12 @@ ambptt_status ambptt_bind(ambptt_ctx* ctx, void* slot_pool, size_t pool_bytes,
  * schedule as if every state had the size of the largest, i.e. slots of the
  * largest size in the same byte budget, for comparison with the sized
  * schedule; 0 by default), "lds_gemm" (fp32 path for large batches: 1, default, runs the gate
- * product with its cell epilogue and the h-adjoint product on LDS-tiled
- * kernels (128 x 128 and 64 x 64 tiles, two workgroups per CU) where they
+ * product with its cell epilogue and the h-adjoint product on the bf16 matrix
+ * cores, each fp32 operand split exactly into three bf16 parts and the six
+ * products that fp32 can tell apart summed in fp32 (with "hadj_launch" and
+ * "prod_split" 1; operands under 4 GiB); elsewhere, as with 2 and without
+ * the split, on LDS-tiled fp32 MFMA kernels
+ * (128 x 128 and 64 x 64 tiles, two workgroups per CU) where they
  * have at least 256 tiles; 2 wherever their shape constraints hold; 0 never:
  * the direct-load kernels), "hadj_launch" (1,
  * default: on the fp32 path for large batches the adjoint's h-adjoint

@@ -1,0 +1,659 @@
+// fp32 products on the bf16 matrix cores (gfx950), for the large-batch
+// recurrent cells: the gate product with the cell epilogue, the adjoint's
+// h-adjoint product, and the copies of the weights that they read.
+//
+// An fp32 value is the exact sum of three bf16 values, a = a0 + a1 + a2 (each
+// the nearest bf16 to what the ones before it leave: 3 x 8 significant bits
+// and two signs cover fp32's 24).  Of the nine products of two such sums the
+// six down to 2^-18 of the largest are formed, a0 b0 + a0 b1 + a1 b0 + a1 b1 +
+// a0 b2 + a2 b0; what is left out is below 2^-26 of |a b|, under fp32's own
+// rounding.  Every product of two bf16 values is exact in the fp32
+// accumulators, so a 32-wide reduction step costs 6
+// v_mfma_f32_16x16x32_bf16 (96 cycles) where v_mfma_f32_16x16x4_f32 takes 8
+// (256 cycles), and it rounds its accumulator 6 times instead of at least 8.
+//
+// Infinities, NaNs and sums past fp32's range do not split (inf - inf): every
+// wave looks at its finished accumulators and, if one is not finite, forms
+// its block again with fp32 MFMAs straight from global memory, so such inputs
+// give what the fp32 kernels give.  zbar is scaled by 2^32 before it is split
+// (and the product by 2^-32), so that gradients down to fp32's smallest
+// normal value keep all three parts in bf16's range.
+//
+// Data flow.  B (the weights, fixed for a pass) is split once per pass into
+// fragment order: the 1 KiB that a wave's MFMA operand needs (16 rows x 32
+// reduction indices, lane l: row l & 15, indices 8 (l >> 4) .. +7) lie
+// together, three planes one after the other.  A (activations, or zbar) is
+// read as fp32 rows and split on its way to LDS: the split's VALU work hides
+// under the MFMAs, and the operand moves 4 bytes per element from L2 instead
+// of 6.  LDS holds two stages of 32 reduction indices.
+//
+// Rounding.  The matrix cores round a bf16 MFMA's sum of products down (not
+// to nearest), a bias that grows with the length of the chain of
+// accumulations: with one chain through the whole reduction db of the
+// 4096-LSTM, a sum over thousands of rows, was 3.4e-6 off (8e-7 with fp32
+// MFMAs).  So each stage's six products are summed from zero and added to the
+// accumulators by VALU adds, which round to nearest, and every other stage
+// multiplies -A and is subtracted, which turns its bias around.
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "ambptt.h"
+#include "kernels.hpp"
+#include "mfma.hpp"
+
+namespace ambptt {
+namespace {
+
+typedef unsigned int u2v __attribute__((ext_vector_type(2)));
+typedef unsigned int u4v __attribute__((ext_vector_type(4)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kSt = 32;                         // reduction indices per stage
+constexpr int kFrag = 1024;                     // bytes of one plane of a 16-row fragment
+constexpr int kBlk = 3 * kFrag;                 // ... of its three planes
+constexpr float kScale = 4294967296.0f;         // 2^32
+constexpr float kUnscale = 1.0f / 4294967296.0f;
+
+__host__ __device__ __forceinline__ int stages(int k) { return (k + kSt - 1) / kSt; }
+
+__device__ __forceinline__ float sigm(float z) { return 1.0f / (1.0f + __expf(-z)); }
+
+__device__ __forceinline__ float wave_sum(float v) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+__device__ __forceinline__ unsigned pk_bf16(float a, float b) {
+  const f2 v = {a, b};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+}
+__device__ __forceinline__ float lo_f(unsigned p) { return __builtin_bit_cast(float, p << 16); }
+__device__ __forceinline__ float hi_f(unsigned p) { return __builtin_bit_cast(float, p & 0xffff0000u); }
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void* base, unsigned bytes) {
+  const unsigned long long p = (unsigned long long)base;
+  const unsigned lo = __builtin_amdgcn_readfirstlane(unsigned(p)), hi = __builtin_amdgcn_readfirstlane(unsigned(p >> 32));
+  void* ub = (void*)(((unsigned long long)hi << 32) | lo);
+  return __builtin_amdgcn_make_buffer_rsrc(ub, 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+// reads past the buffer's end return zero
+__device__ __forceinline__ u4v bload(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
+}
+
+// the three planes of a pair of values
+__device__ __forceinline__ void split2(float a, float b, unsigned& p0, unsigned& p1, unsigned& p2) {
+  p0 = pk_bf16(a, b);
+  const float a1 = a - lo_f(p0), b1 = b - hi_f(p0);
+  p1 = pk_bf16(a1, b1);
+  p2 = pk_bf16(a1 - lo_f(p1), b1 - hi_f(p1));
+}
+
+__device__ __forceinline__ void tile_of(int i, int mt, int nt, int* tm, int* tn) {
+  if (nt % 8 == 0) {  // the row tiles of one column tile share an XCD
+    const int xcd = i & 7, k = i >> 3;
+    *tn = xcd * (nt >> 3) + k / mt;
+    *tm = k % mt;
+  } else {
+    *tm = i % mt;
+    *tn = i / mt;
+  }
+}
+
+// One workgroup's product on a TM x TN tile: 4 or 8 waves of (TM / WM) x
+// (TN / WN).  A: rows of [x | h], fp32; B: planes in fragment order.
+template <int TM, int TN, int WM, int WN>
+struct Tile {
+  static constexpr int NW = WM * WN, NT = 64 * NW;
+  static constexpr int MI = TM / WM / 16, NI = TN / WN / 16;
+  static constexpr int PA = TM * 8 / NT;            // float4 of A per thread and stage
+  static constexpr int PB = TN / 16 * 3 / NW;       // 16-byte pieces of B per thread and stage
+  static constexpr int ABYTES = TM / 16 * kBlk, BBYTES = TN / 16 * kBlk;
+  static constexpr int STAGE = ABYTES + BBYTES;
+  static_assert(TM * 8 % NT == 0 && TN / 16 * 3 % NW == 0 && MI % 2 == 0, "whole loads per thread, row blocks in pairs");
+
+  // A's rows are [x | h], x: [M][D], h: [M][H], each padded to whole stages
+  // (TWO false: h alone).  bblk(b) is the packed block row of the tile's
+  // 16-column block b; kb its 32-wide steps.  What a padded stage reads of A
+  // past the end of a row meets zeros of B.
+  template <bool TWO, bool SCALE, class BBlk>
+  static __device__ __forceinline__ void run(const float* x, const float* h, int M, int D, int H, int m0,
+                                             const char* Bp, unsigned bbytes, int kb, int st0, int st1, BBlk bblk,
+                                             char* lds, f4 (&acc)[MI][NI]) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int r = lane & 15, q = lane >> 4;
+    const int kx = TWO ? (D + kSt - 1) / kSt : 0;  // x's stages
+    // A loader: thread t takes float4 t % 8 of rows t / 8 + (NT / 8) p of a
+    // stage, so 8 lanes read one 128-byte line.  In LDS the 16 bytes of (row
+    // r, indices 8 g .. +7) of a fragment lie in slot 16 g + (r ^ swz(g)),
+    // swz = 0, 12, 4, 8: the four g of a write then fall on distinct banks,
+    // and the lanes that one pass of a 16-byte read serves (0-3, 12-15 and
+    // 20-27 of a half wave) still do
+    const int lr = tid >> 3, c4 = tid & 7;
+    const auto swz = [](int g) { return 4 * ((g >> 1) ^ (3 * (g & 1))); };
+    const unsigned xbytes = unsigned(M) * unsigned(D) * 4u, hbytes = unsigned(M) * unsigned(H) * 4u;
+    static_assert(NT % 128 == 0, "a thread's rows share their place in a fragment");
+    const int aoff = (lr >> 4) * kBlk + (16 * (c4 >> 1) + ((lr & 15) ^ swz(c4 >> 1))) * 16 + 8 * (c4 & 1);
+    // B loader: wave w moves PB of the tile's 3 TN / 16 plane fragments
+    unsigned bsrc[PB];
+#pragma unroll
+    for (int p = 0; p < PB; ++p) {
+      const int f = wave * PB + p;  // block f / 3, plane f % 3
+      bsrc[p] = unsigned(bblk(f / 3)) * unsigned(kb) * unsigned(kBlk) + unsigned(f % 3) * unsigned(kFrag);
+    }
+    const int boff = ABYTES + wave * PB * kFrag + lane * 16;
+
+    // piece p of stage st to registers: float4 p of A, or (p = PA) the B
+    // planes; of a stage past the last, its A again and zeros for B (the
+    // stages go in pairs)
+    f4 ra[PA];
+    u4v rb[PB];
+    auto gload = [&](int st_, int p) {
+      const int st = min(st_, st1 - 1);
+      if (p < PA) {
+        // selects, not a branch: the stage stays one block for the scheduler
+        const bool inx = TWO && st < kx;
+        const unsigned long long base = inx ? (unsigned long long)x : (unsigned long long)h;
+        const __amdgpu_buffer_rsrc_t ru = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, inx ? xbytes : hbytes, 0x00020000);
+        const unsigned m = unsigned(min(m0 + lr + (NT / 8) * p, M - 1));  // rows past M: clamped, their results unused
+        ra[p] = __builtin_bit_cast(f4, bload(ru, m * unsigned(inx ? 4 * D : 4 * H) + 16u * unsigned(c4),
+                                             unsigned(inx ? st : st - kx) * 128u));
+      } else {
+#pragma unroll
+        for (int f = 0; f < PB; ++f)
+          rb[f] = bload(rsrc(Bp, st_ < st1 ? bbytes : 0u), 16u * unsigned(lane), bsrc[f] + unsigned(st) * unsigned(kBlk));
+      }
+    };
+    // piece p, split, to LDS; the stages of buffer 1 hold -A
+    auto put = [&](int buf, int p) {
+      char* s = lds + buf * STAGE;
+      if (p < PA) {
+        f4 v = ra[p];
+        if (SCALE) v *= buf ? -kScale : kScale;
+        else if (buf) v = -v;
+        u2v p0, p1, p2;
+        unsigned t0, t1, t2;
+        split2(v.x, v.y, t0, t1, t2);
+        p0.x = t0, p1.x = t1, p2.x = t2;
+        split2(v.z, v.w, t0, t1, t2);
+        p0.y = t0, p1.y = t1, p2.y = t2;
+        char* d = s + aoff + p * (NT / 128) * kBlk;
+        *(u2v*)d = p0;
+        *(u2v*)(d + kFrag) = p1;
+        *(u2v*)(d + 2 * kFrag) = p2;
+      } else {
+#pragma unroll
+        for (int f = 0; f < PB; ++f) *(u4v*)(s + boff + f * kFrag) = rb[f];
+      }
+    };
+    const int ard = (wm * MI) * kBlk + (16 * q + (r ^ swz(q))) * 16;
+    const int brd = ABYTES + (wn * NI) * kBlk + lane * 16;
+    bf16x8 b[3][NI], a[2][3];
+    auto lda = [&](int buf, int i) {
+#pragma unroll
+      for (int pl = 0; pl < 3; ++pl) a[i & 1][pl] = *(const bf16x8*)(lds + buf * STAGE + ard + i * kBlk + pl * kFrag);
+    };
+    auto ldb = [&](int buf, int pl) {
+#pragma unroll
+      for (int j = 0; j < NI; ++j) b[pl][j] = *(const bf16x8*)(lds + buf * STAGE + brd + j * kBlk + pl * kFrag);
+    };
+
+#pragma unroll
+    for (int p = 0; p <= PA; ++p) gload(st0, p);
+#pragma unroll
+    for (int p = 0; p <= PA; ++p) {
+      put(0, p);
+      gload(st0 + 1, p);
+    }
+    __syncthreads();
+    lda(0, 0);
+    ldb(0, 2);
+    ldb(0, 1);
+    ldb(0, 0);
+    f4 tl[NI];  // the last row block's sums, added one block later
+#pragma unroll
+    for (int j = 0; j < NI; ++j) tl[j] = f4{0.f, 0.f, 0.f, 0.f};
+    // A stage is MI row blocks of 6 NI MFMAs.  In the blocks but the last the
+    // next stage goes to the other buffer, a piece at a time, and the piece's
+    // loads for the stage after that are issued (so a load has a whole stage
+    // to arrive).  The one barrier of a stage comes before its last block,
+    // whose operands are in registers by then: during that block the next
+    // stage's first operands are read, each plane of B once its last use is
+    // issued, and the matrix cores find them there after it.
+    auto stage = [&](int st, auto cur_) __attribute__((always_inline)) {
+      constexpr int cur = decltype(cur_)::value;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const bool tail = i == MI - 1;
+        if (tail) __syncthreads();
+        f4 t[NI];
+#pragma unroll
+        for (int j = 0; j < NI; ++j) t[j] = f4{0.f, 0.f, 0.f, 0.f};
+        auto mul = [&](int pa, int pb) {
+#pragma unroll
+          for (int j = 0; j < NI; ++j)
+            t[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i & 1][pa], b[pb][j], t[j], 0, 0, 0);
+        };
+        if (!tail) {
+          lda(cur, i + 1);
+          mul(0, 2);
+          mul(1, 1);
+          mul(0, 1);
+          mul(2, 0);
+          mul(1, 0);
+          mul(0, 0);
+#pragma unroll
+          for (int p = 0; p <= PA; ++p)
+            if (p * (MI - 1) / (PA + 1) == i) {
+              put(cur ^ 1, p);
+              gload(st + 2, p);
+            }
+        } else {
+          lda(cur ^ 1, 0);
+          mul(0, 2);
+          __builtin_amdgcn_sched_barrier(0);
+          ldb(cur ^ 1, 2);
+          mul(1, 1);
+          mul(0, 1);
+          __builtin_amdgcn_sched_barrier(0);
+          ldb(cur ^ 1, 1);
+          mul(2, 0);
+          mul(1, 0);
+          mul(0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          ldb(cur ^ 1, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {  // (the row block before the first is the stage before's last)
+          if ((i == 0) != (cur == 1)) acc[(i + MI - 1) % MI][j] -= tl[j];
+          else acc[i == 0 ? MI - 1 : i - 1][j] += tl[j];
+          tl[j] = t[j];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    for (int st = st0; st < st1; st += 2) {
+      stage(st, std::integral_constant<int, 0>{});
+      stage(st + 1, std::integral_constant<int, 1>{});
+    }
+#pragma unroll
+    for (int j = 0; j < NI; ++j) acc[MI - 1][j] -= tl[j];
+    if (SCALE) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) acc[i][j] *= kUnscale;
+    }
+    __syncthreads();  // the last stage's reads of the buffers are done
+  }
+
+  // whether any of the wave's accumulators is an infinity or a NaN
+  static __device__ __forceinline__ bool any_bad(const f4 (&acc)[MI][NI]) {
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) bad |= !(fabsf(acc[i][j][v]) <= 3.402823466e38f);
+    return __any(bad);
+  }
+
+  // The wave's block by fp32 MFMAs from global memory; bval(j, k) is B of the
+  // lane's column (l & 15) of the wave's column block j at reduction indices
+  // k .. k + 3.  K and D are multiples of 16.
+  template <class BVal>
+  static __device__ __forceinline__ void exact(const float* x, const float* h, int M, int D, int H, int m0, int k0,
+                                               int k1, BVal bval, f4 (&acc)[MI][NI]) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave / WN;
+    const int r = lane & 15, q = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int k = k0; k < k1; k += 16) {
+      f4 av[MI], bv[NI];
+      const bool inx = k < D;
+      const float* base = inx ? x : h;
+      const int ld = inx ? D : H, kk = (inx ? k : k - D) + 4 * q;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) av[i] = *(const f4*)(base + (size_t)min(m0 + (wm * MI + i) * 16 + r, M - 1) * ld + kk);
+#pragma unroll
+      for (int j = 0; j < NI; ++j) bv[j] = bval(j, k + 4 * q);
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j) acc[i][j] = mfma_f32_16x16x4(av[i][c], bv[j][c], acc[i][j]);
+    }
+  }
+};
+
+// ---- gate product with the cell epilogue --------------------------------------
+// Tile: TM batch rows x TN gate columns = U = TN / G units of all G gates
+// (16-column block b of the tile: gate b / (U / 16)).  The finished tile goes
+// to LDS, and every thread then takes four consecutive units of a row: the
+// epilogue's global accesses are 16 bytes per lane.
+template <int G, int MODE, int TM, int TN, int WM, int WN>
+__global__ __launch_bounds__(64 * WM * WN) void cell_f32x3(StepArgs a) {
+  using T = Tile<TM, TN, WM, WN>;
+  constexpr int U = TN / G, UB = U / 16, LZ = TN + 4;
+  constexpr int LDS = 2 * T::STAGE > TM * LZ * 4 ? 2 * T::STAGE : TM * LZ * 4;
+  __shared__ __attribute__((aligned(16))) char lds[LDS];
+  __shared__ float red[T::NW];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int r = lane & 15, q = lane >> 4;
+  const int B = a.B, D = a.D, H = a.H, K1 = D + H, GH = G * H;
+  const int mt = (B + TM - 1) / TM, nt = (H + U - 1) / U;
+  int tm, tn;
+  tile_of(blockIdx.x, mt, nt, &tm, &tn);
+  const int m0 = tm * TM, j0 = tn * U;
+  const int hb = H / 16;
+  // units past H (the last tile): the last 16 units again, unused
+  auto bblk = [&](int b) { return (b / UB) * hb + min(j0 / 16 + b % UB, hb - 1); };
+
+  f4 acc[T::MI][T::NI];
+#pragma unroll
+  for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+    for (int j = 0; j < T::NI; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+  const int kb = stages(D) + stages(H);
+  T::template run<true, false>((const float*)a.x, (const float*)a.h, B, D, H, m0, (const char*)a.Wx3,
+                               unsigned(GH / 16) * unsigned(kb) * unsigned(kBlk), kb, 0, kb, bblk, lds, acc);
+  if (T::any_bad(acc)) {
+    const float* W = (const float*)a.W;
+    T::exact((const float*)a.x, (const float*)a.h, B, D, H, m0, 0, K1,
+             [&](int j, int k) {
+               return *(const f4*)(W + (size_t)(16 * bblk(wn * T::NI + j) + r) * K1 + k);
+             },
+             acc);
+  }
+  float* z = (float*)lds;
+#pragma unroll
+  for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+    for (int j = 0; j < T::NI; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        z[((wm * T::MI + i) * 16 + 4 * q + v) * LZ + (wn * T::NI + j) * 16 + r] = acc[i][j][v];
+  __syncthreads();
+
+  float lterm = 0.f;
+  constexpr int TPR = U / 4;  // threads per row
+  const int j = j0 + 4 * (tid % TPR);
+  if (j < H) {
+    f4 bias[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) bias[g] = *(const f4*)(a.bias + g * H + j);
+#pragma unroll 2
+    for (int row = tid / TPR; row < TM; row += T::NT / TPR) {
+      const int m = m0 + row;
+      if (m >= B) break;
+      const size_t o = (size_t)m * H + j;
+      const float* zr = z + row * LZ + (j - j0);
+      f4 h1, c1, tc, ig, fg, gg, og, cold;
+      if (G == 4) {
+        const f4 z0 = *(const f4*)zr + bias[0], z1 = *(const f4*)(zr + U) + bias[G > 1 ? 1 : 0];
+        const f4 z2 = *(const f4*)(zr + 2 * U) + bias[G > 1 ? 2 : 0], z3 = *(const f4*)(zr + 3 * U) + bias[G > 1 ? 3 : 0];
+        cold = *(const f4*)(a.c + o);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          ig[e] = sigm(z0[e]);
+          fg[e] = sigm(z1[e]);
+          gg[e] = tanhf(z2[e]);
+          og[e] = sigm(z3[e]);
+          c1[e] = fg[e] * cold[e] + ig[e] * gg[e];
+          tc[e] = tanhf(c1[e]);
+          h1[e] = og[e] * tc[e];
+        }
+      } else {
+        const f4 z0 = *(const f4*)zr + bias[0];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h1[e] = tanhf(z0[e]);
+      }
+      if (MODE == kForward) {
+        *(f4*)((float*)a.h_out + o) = h1;
+        if (G == 4) *(f4*)(a.c_out + o) = c1;
+        continue;
+      }
+      // adjoint: loss term of h_{t+1} and its seed dL/dh_{t+1}
+      f4 hbar = {0.f, 0.f, 0.f, 0.f};
+      if (!a.first) {  // the product's partial sums, in order
+        hbar = *(const f4*)(a.hbar_in + o);
+        for (int ps = 1; ps < a.hbar_parts; ++ps) hbar += *(const f4*)(a.hbar_in + o + (size_t)ps * B * H);
+      }
+      if (a.loss == AMBPTT_LOSS_MEAN_SQ_ALL) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          hbar[e] += 2.f * h1[e] * a.inv_bh;
+          lterm += h1[e] * h1[e];
+        }
+      } else if (a.last) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool sq = a.loss == AMBPTT_LOSS_HALF_SQ_LAST;
+          hbar[e] += sq ? h1[e] : a.inv_bh;
+          lterm += sq ? h1[e] * h1[e] : h1[e];
+        }
+      }
+      float* zo = (float*)a.zbar_out + (size_t)m * GH + j;
+      if (G == 4) {
+        f4 cb = {0.f, 0.f, 0.f, 0.f};
+        if (!a.first) cb = *(const f4*)(a.cbar_in + o);
+        f4 d0, d1, d2, d3, cn;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float ob = hbar[e] * tc[e];
+          const float ch = cb[e] + hbar[e] * og[e] * (1.f - tc[e] * tc[e]);
+          d0[e] = ch * gg[e] * ig[e] * (1.f - ig[e]);
+          d1[e] = ch * cold[e] * fg[e] * (1.f - fg[e]);
+          d2[e] = ch * ig[e] * (1.f - gg[e] * gg[e]);
+          d3[e] = ob * og[e] * (1.f - og[e]);
+          cn[e] = ch * fg[e];
+        }
+        *(f4*)zo = d0;
+        *(f4*)(zo + H) = d1;
+        *(f4*)(zo + 2 * H) = d2;
+        *(f4*)(zo + 3 * H) = d3;
+        *(f4*)(a.cbar_out + o) = cn;
+      } else {
+        f4 d;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = hbar[e] * (1.f - h1[e] * h1[e]);
+        *(f4*)zo = d;
+      }
+      *(f4*)((float*)a.hwin_out + o) = *(const f4*)((const float*)a.h + o);
+    }
+  }
+  if (MODE == kAdjoint) {  // the waves' loss terms, summed in wave order
+    const float s = wave_sum(lterm);
+    if (lane == 0) red[wave] = s;
+    __syncthreads();
+    if (tid == 0) {
+      double t = 0.0;
+      for (int w = 0; w < T::NW; ++w) t += (double)red[w];
+      a.loss_acc[blockIdx.x] += t;
+    }
+  }
+}
+
+// ---- h-adjoint product: out = zbar W_h, the reduction split --------------------
+// Part s of `parts` contiguous runs of stages goes to out + s M N; the
+// adjoint (or sum_parts) adds the parts in order.
+template <int TM, int TN, int WM, int WN>
+__global__ __launch_bounds__(64 * WM * WN) void prod_f32x3(ProdArgs a, int parts) {
+  using T = Tile<TM, TN, WM, WN>;
+  __shared__ __attribute__((aligned(16))) char lds[2 * T::STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int r = lane & 15, q = lane >> 4;
+  const int M = a.M, N = a.N, K = a.K;
+  const int mt = (M + TM - 1) / TM, nt = (N + TN - 1) / TN;
+  int tm, tc;
+  tile_of(blockIdx.x, mt, nt * parts, &tm, &tc);
+  const int tn = tc / parts, part = tc % parts;
+  const int m0 = tm * TM, n0 = tn * TN;
+  const int kb = stages(K);
+  const int st0 = int((long)part * kb / parts), st1 = int((long)(part + 1) * kb / parts);
+  auto bblk = [&](int b) { return min(n0 / 16 + b, N / 16 - 1); };  // columns past N: the last 16 again, unused
+  f4 acc[T::MI][T::NI];
+#pragma unroll
+  for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+    for (int j = 0; j < T::NI; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+  T::template run<false, true>((const float*)a.A, (const float*)a.A, M, 0, K, m0, (const char*)a.B,
+                               unsigned(N / 16) * unsigned(kb) * unsigned(kBlk), kb, st0, st1, bblk, lds, acc);
+  if (T::any_bad(acc)) {
+    const float* W = a.Bf;  // B(k, n) = W[k ldb + n]
+    T::exact((const float*)a.A, (const float*)a.A, M, 0, K, m0, st0 * kSt, min(st1 * kSt, K),
+             [&](int j, int k) {
+               const float* s = W + (size_t)k * a.ldb + 16 * bblk(wn * T::NI + j) + r;
+               return f4{s[0], s[a.ldb], s[2 * (size_t)a.ldb], s[3 * (size_t)a.ldb]};
+             },
+             acc);
+  }
+  float* out = a.out + (size_t)part * M * N;
+#pragma unroll
+  for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int m = m0 + (wm * T::MI + i) * 16 + 4 * q + v;
+      if (m >= M) continue;
+#pragma unroll
+      for (int j = 0; j < T::NI; ++j) {
+        const int n = n0 + (wn * T::NI + j) * 16 + r;
+        if (n < N) out[(size_t)m * N + n] = acc[i][j][v];
+      }
+    }
+}
+
+__global__ void sum_parts_f32(const float* __restrict__ p, int parts, size_t n4, float* __restrict__ out) {
+  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+  if (i >= n4) return;
+  f4 s = ((const f4*)p)[i];
+  for (int k = 1; k < parts; ++k) s += ((const f4*)p)[i + (size_t)k * n4];
+  ((f4*)out)[i] = s;
+}
+
+// dst <- the planes of src's N rows of K values in fragment order, K padded
+// with zeros to whole stages: steps kb0 .. of the kb steps of a block row.  A
+// thread makes one lane's 16 bytes of the three planes.  TR: src(n, k) =
+// src[k ld + n] (the columns of W_h).
+template <bool TR>
+__global__ __launch_bounds__(256) void pack_f32x3(const float* __restrict__ src, int N, int K, int ld, int kb, int kb0,
+                                                  char* __restrict__ dst) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // the four waves of a block take neighbouring fragments along the rows of src
+  const int nb = TR ? blockIdx.y * 4 + wave : blockIdx.y, ks = TR ? blockIdx.x : blockIdx.x * 4 + wave;
+  if (nb >= N / 16 || ks >= stages(K)) return;
+  const int n = nb * 16 + (lane & 15), k = ks * kSt + 8 * (lane >> 4);
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    v[e] = k < K ? src[TR ? (size_t)(k + e) * ld + n : (size_t)n * ld + k + e] : 0.f;  // K is a multiple of 8
+  u4v p0, p1, p2;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    unsigned t0, t1, t2;
+    split2(v[2 * e], v[2 * e + 1], t0, t1, t2);
+    p0[e] = t0, p1[e] = t1, p2[e] = t2;
+  }
+  char* d = dst + ((size_t)nb * kb + kb0 + ks) * kBlk + lane * 16;
+  *(u4v*)d = p0;
+  *(u4v*)(d + kFrag) = p1;
+  *(u4v*)(d + 2 * kFrag) = p2;
+}
+
+}  // namespace
+
+size_t f32x3_bytes(int N, int K0, int K1) { return size_t(N / 16) * size_t(stages(K0) + stages(K1)) * kBlk; }
+
+hipError_t launch_pack_f32x3(const float* src, int N, int K0, int K1, int ld, bool transposed, void* dst, hipStream_t s) {
+  if (N < 16 || N % 16 || K0 % 8 || K1 % 8 || K0 < 0 || K1 < 8) return hipErrorInvalidValue;
+  const int kb = stages(K0) + stages(K1);
+  for (int seg = 0; seg < 2; ++seg) {
+    const int K = seg ? K1 : K0, kb0 = seg ? stages(K0) : 0;
+    if (K == 0) continue;
+    const float* p = src + (seg ? (transposed ? size_t(K0) * ld : size_t(K0)) : 0);
+    if (transposed)
+      hipLaunchKernelGGL((pack_f32x3<true>), dim3(stages(K), (N / 16 + 3) / 4), dim3(256), 0, s, p, N, K, ld, kb, kb0,
+                         (char*)dst);
+    else
+      hipLaunchKernelGGL((pack_f32x3<false>), dim3((stages(K) + 3) / 4, N / 16), dim3(256), 0, s, p, N, K, ld, kb, kb0,
+                         (char*)dst);
+  }
+  return hipGetLastError();
+}
+
+bool f32x3_fits(int G, int B, int D, int H) {
+  const unsigned long long lim = 1ull << 32;  // buffer offsets are 32-bit
+  return (G == 1 || G == 4) && B >= 1 && D >= 0 && D % 16 == 0 && H >= 16 && H % 16 == 0 &&
+         4ull * B * H * G + 4096 < lim && 4ull * B * D + 4096 < lim && f32x3_bytes(G * H, D, H) < lim &&
+         f32x3_bytes(H, 0, G * H) < lim;
+}
+
+namespace {
+template <int G, int MODE>
+hipError_t cell_launch(const StepArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  const auto tiles = [&](int tm, int tn) { return ((a.B + tm - 1) / tm) * ((a.H + tn / G - 1) / (tn / G)); };
+  // 256 x 128 tiles move the fewest operand bytes per MFMA and fill a CU with
+  // one workgroup, so they need most of the 256 CUs; fewer tiles go 128 x 64,
+  // two workgroups to a CU (300 x 4096 x 1120: 64 tiles of 256 x 128, 192 of
+  // 128 x 64)
+  if (tiles(256, 128) >= 192) {
+    hipExtLaunchKernelGGL((cell_f32x3<G, MODE, 256, 128, 4, 2>), dim3(tiles(256, 128)), dim3(512), 0, s, e0, e1, 0, a);
+  } else {
+    hipExtLaunchKernelGGL((cell_f32x3<G, MODE, 128, 64, 4, 1>), dim3(tiles(128, 64)), dim3(256), 0, s, e0, e1, 0, a);
+  }
+  return hipGetLastError();
+}
+}  // namespace
+
+int cell_f32x3_tiles(int G, int B, int H) {  // the most workgroups that any of its launches has
+  return ((B + 127) / 128) * ((H + 64 / G - 1) / (64 / G));
+}
+
+hipError_t launch_cell_f32x3(int G, int mode, const StepArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  if (!f32x3_fits(G, a.B, a.D, a.H) || !a.Wx3 || (mode == kAdjoint && !a.first && !a.hbar_in)) return hipErrorInvalidValue;
+  if (mode != kForward && mode != kAdjoint) return hipErrorInvalidValue;
+  if (G == 4) return mode == kForward ? cell_launch<4, kForward>(a, s, e0, e1) : cell_launch<4, kAdjoint>(a, s, e0, e1);
+  return mode == kForward ? cell_launch<1, kForward>(a, s, e0, e1) : cell_launch<1, kAdjoint>(a, s, e0, e1);
+}
+
+int prod_f32x3_parts(int M, int N, int K) {
+  const int tiles = ((M + 255) / 256) * ((N + 127) / 128);
+  int parts = 1;
+  while (parts < kProdSplitMax && tiles * parts * 2 <= 256 && (K / kSt) / (2 * parts) >= 16) parts *= 2;
+  return parts;
+}
+
+hipError_t launch_prod_f32x3(const ProdArgs& a, int parts, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  if (a.M < 1 || a.N < 16 || a.N % 16 || a.K < 16 || a.K % 16 || a.add || !a.Bf || parts < 1 || parts > kProdSplitMax ||
+      parts > (a.K + kSt - 1) / kSt)
+    return hipErrorInvalidValue;
+  const int tiles = ((a.M + 255) / 256) * ((a.N + 127) / 128);
+  if (tiles * parts >= 192) {
+    hipExtLaunchKernelGGL((prod_f32x3<256, 128, 4, 2>), dim3(tiles * parts), dim3(512), 0, s, e0, e1, 0, a, parts);
+  } else {
+    const int small = ((a.M + 127) / 128) * ((a.N + 63) / 64);
+    hipExtLaunchKernelGGL((prod_f32x3<128, 64, 4, 1>), dim3(small * parts), dim3(256), 0, s, e0, e1, 0, a, parts);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_sum_parts_f32(const float* p, int parts, size_t n, float* out, hipStream_t s, hipEvent_t e0,
+                                hipEvent_t e1) {
+  if (n % 4 || parts < 1) return hipErrorInvalidValue;
+  hipExtLaunchKernelGGL(sum_parts_f32, dim3(unsigned((n / 4 + 255) / 256)), dim3(256), 0, s, e0, e1, 0, p, parts, n / 4,
+                        out);
+  return hipGetLastError();
+}
+
+}  // namespace ambptt

@@ -42,6 +42,7 @@ struct StepArgs {
   float inv_bh;          // 1 / (B H)
   int ld_wht = 0;        // row stride of WhT in elements (0: G*H)
   int hbar_parts = 1;    // hbar_in holds this many [B][H] partial sums, added in order
+  const void* Wx3 = nullptr;  // the split planes of W (launch_pack_f32x3), for the cell on bf16 matrix cores
 };
 
 // Weight-gradient window: dW[k][c] += sum_r Z[r][k] X[r][c], db[k] += sum_r Z[r][k],
@@ -84,7 +85,8 @@ struct ProdArgs {
   const float* add;
   float* out;
   int M, N, K;
-  int ldb = 0;  // row stride of B in elements (0: K)
+  int ldb = 0;  // row stride of B in elements (0: K); of Bf where that is given
+  const float* Bf = nullptr;  // prod_f32x3: B itself, B(k, n) = Bf[k ldb + n] (B holds its split planes)
 };
 
 // One launch of the MLP whose layers change width (mlp_f32.hip):
@@ -193,6 +195,22 @@ constexpr int kProdSplitMax = 4;
 int prod_split_f32_parts(int M, int N, int K);  // 1: the split does not fit or does not pay
 hipError_t launch_prod_split_f32(const ProdArgs& a, int parts, hipStream_t s, hipEvent_t e0 = nullptr,
                                  hipEvent_t e1 = nullptr);
+// fp32 products on the bf16 matrix cores (gemm_f32x3.hip): operands split into
+// three bf16 planes, six products.  D and H multiples of 16, buffers under 4 GiB.
+bool f32x3_fits(int G, int B, int D, int H);
+// bytes of the planes of an [N][K0 + K1] operand (each segment padded to
+// whole stages), and the copy (transposed: src(n, k) = src[k ld + n])
+size_t f32x3_bytes(int N, int K0, int K1);
+hipError_t launch_pack_f32x3(const float* src, int N, int K0, int K1, int ld, bool transposed, void* dst, hipStream_t s);
+int cell_f32x3_tiles(int G, int B, int H);
+hipError_t launch_cell_f32x3(int G, int mode, const StepArgs& a, hipStream_t s, hipEvent_t e0 = nullptr,
+                             hipEvent_t e1 = nullptr);
+int prod_f32x3_parts(int M, int N, int K);
+hipError_t launch_prod_f32x3(const ProdArgs& a, int parts, hipStream_t s, hipEvent_t e0 = nullptr,
+                             hipEvent_t e1 = nullptr);
+// out = the sum, in order, of `parts` arrays of n floats
+hipError_t launch_sum_parts_f32(const float* p, int parts, size_t n, float* out, hipStream_t s,
+                                hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 // 128 x 128-tile fp32 weight gradient for GH, D + H >= 256 (launch_dw picks it when it fits).
 bool dw_f32_big_fits(const DwArgs& a);
 hipError_t launch_dw_f32_big(const DwArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1);

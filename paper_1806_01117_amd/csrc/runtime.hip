@@ -66,6 +66,9 @@ struct Layout {
   size_t h_bytes = 0, c_bytes = 0, state_bytes = 0, stride = 0;
   size_t off_live[2] = {0, 0}, off_wht = 0, off_zbar = 0, off_hwin = 0, off_cbar[2] = {0, 0};
   size_t off_wpk = 0, off_whpk = 0;  // wide bf16 cell: W and W_h^T in fragment order
+  // large-batch fp32 cell on the bf16 matrix cores: W's and W_h^T's split planes
+  bool x3 = false;
+  size_t off_wx3 = 0, off_whx3 = 0;
   int ld_wht = 0;        // row stride of WhT in elements
   size_t off_loss = 0, off_lossout = 0, total = 0;
   int loss_slots = 0;
@@ -200,6 +203,8 @@ Layout make_layout(const ambptt_problem* p, int window) {
   if (!L.small && !L.mlp && !L.mlpv && p->dtype == AMBPTT_F32 &&
       cell_gemm_f32_fits(L.G, p->batch, p->input, p->hidden))
     L.loss_slots = std::max(L.loss_slots, cell_gemm_f32_tiles(L.G, p->batch, p->hidden));
+  L.x3 = !L.small && !L.mlp && !L.mlpv && p->dtype == AMBPTT_F32 && f32x3_fits(L.G, p->batch, p->input, p->hidden);
+  if (L.x3) L.loss_slots = std::max(L.loss_slots, cell_f32x3_tiles(L.G, p->batch, p->hidden));
   size_t o = 0;
   L.off_live[0] = o; o += L.stride;
   L.off_live[1] = o; o += L.stride;
@@ -239,6 +244,16 @@ Layout make_layout(const ambptt_problem* p, int window) {
     L.off_P = o; o += align_up(2 * mt * (ng / size_t(L.r_S)) * size_t(p->hidden) * 16 * 4);
     L.off_dWp = o; o += align_up(mt * GH * K1 * 4);
     L.off_dbp = o; o += align_up(mt * GH * 4);
+  }
+  if (L.x3) {
+    const size_t planes = align_up(f32x3_bytes(int(GH), p->input, p->hidden)) + align_up(f32x3_bytes(p->hidden, 0, int(GH)));
+    // a workspace that fits ambptt_run_noalloc's scratch array stays within it
+    if (o <= kScratchBytes && o + planes > kScratchBytes) {
+      L.x3 = false;
+    } else {
+      L.off_wx3 = o; o += align_up(f32x3_bytes(int(GH), p->input, p->hidden));
+      L.off_whx3 = o; o += align_up(f32x3_bytes(p->hidden, 0, int(GH)));
+    }
   }
   L.total = o;
   return L;
@@ -567,6 +582,9 @@ struct Exec {
   bool lds_prod = false;   // ... whose h-adjoint products run on the LDS-tiled kernel
   float* hbuf = nullptr;   // the adjoint's product (fp32 [B][H]) on those two paths
   int hparts = 1;          // split parts of the fp32 LDS-tiled product (summed by the adjoint)
+  bool x3 = false;         // ... both products on the bf16 matrix cores (split operands)
+  void* Wx3 = nullptr;     // their split planes of W and W_h^T
+  void* WhX3 = nullptr;
 
   Exec(ambptt_ctx* c, const void* x_, const void* W_, const float* b_)
       : C(c), L(c->L), p(c->p), x((const char*)x_), W(W_), b(b_), slot_t(c->pend.size(), -1) {
@@ -582,6 +600,15 @@ struct Exec {
                  (C->lds_gemm == 2 || cell_gemm_f32_tiles(G, B, H) >= 256);
       lds_prod = sep32 && C->lds_gemm > 0 && prod_gemm_f32_fits(B, H, G * H) &&
                  (C->lds_gemm == 2 || prod_gemm_f32_tiles(B, H) >= 256);
+      // by default, with the h-adjoint product as a launch of its own, the
+      // split-operand kernels take both products
+      x3 = L.x3 && sep32 && C->lds_gemm == 1 && C->prod_split;
+      if (x3) {
+        lds_cell = lds_prod = false;
+        Wx3 = C->ws + L.off_wx3;
+        WhX3 = C->ws + L.off_whx3;
+        hparts = prod_f32x3_parts(B, H, G * H);
+      }
       // the split parts are summed by the LDS-tiled adjoint only
       if (lds_prod && lds_cell && C->prod_split) hparts = prod_split_f32_parts(B, H, G * H);
     }
@@ -690,9 +717,17 @@ struct Exec {
     a.bias = b;
     a.WhT = WhT;
     a.ld_wht = L.ld_wht;
+    a.Wx3 = Wx3;
     a.loss = p.loss;
     a.inv_bh = 1.0f / float((double)p.batch * p.hidden);
     return a;
+  }
+
+  // zbar W_h on the split planes, into `hparts` partial sums at `out`
+  ProdArgs x3_prod(const void* zbar, float* out) const {
+    ProdArgs pa{zbar, WhX3, nullptr, out, p.batch, p.hidden, L.G * p.hidden, p.input + p.hidden};
+    pa.Bf = (const float*)W + p.input;
+    return pa;
   }
 
   // the fp32 h-adjoint product out = zbar W_h
@@ -706,6 +741,7 @@ struct Exec {
       w.W = Wpk;
       return launch_cell_wide(L.G, mode, w, C->cs, e0, e1);
     }
+    if (x3 && mode != kFinal) return launch_cell_f32x3(L.G, mode, a, C->cs, e0, e1);
     if (lds_cell && (mode == kForward || (mode == kAdjoint && (a.first || a.hbar_in))))
       return launch_cell_gemm_f32(L.G, mode, a, C->cs, e0, e1);
     return L.small ? launch_step_small(L.G, p.dtype == AMBPTT_BF16, mode, a, C->cs, e0, e1)
@@ -851,7 +887,9 @@ struct Exec {
       a.loss_acc = (double*)(C->ws + L.off_loss);
       if ((wide || sep32) && !first) {  // hbar_{t+1} = zbar_{t+1} W_h
         ProdArgs pa{a.zbar_in, wide ? WhPk : WhT, nullptr, hbuf, p.batch, p.hidden, L.G * p.hidden, L.ld_wht};
+        if (x3) pa = x3_prod(a.zbar_in, hbuf);
         s = timed(AMBPTT_K_HADJ, [&](hipEvent_t e0, hipEvent_t e1) {
+          if (x3) return launch_prod_f32x3(pa, hparts, C->cs, e0, e1);
           if (hparts > 1) return launch_prod_split_f32(pa, hparts, C->cs, e0, e1);
           return wide ? launch_prod_nt(pa, C->cs, e0, e1) : prod32(pa, e0, e1);
         });
@@ -953,6 +991,15 @@ struct Exec {
     a.cbar_in = cbar(0);
     a.dh0 = dh0;
     a.dc0 = dc0;
+    if (x3) {  // dL/dh_0 = zbar_0 W_h in parts, then their sum
+      ambptt_status s = timed(AMBPTT_K_OTHER, [&](hipEvent_t e0, hipEvent_t e1) {
+        return launch_prod_f32x3(x3_prod(a.zbar_in, hbuf), hparts, C->cs, e0, e1);
+      });
+      if (s != AMBPTT_OK) return s;
+      HIPCK(launch_sum_parts_f32(hbuf, hparts, (size_t)p.batch * p.hidden, dh0, C->cs));
+      if (L.G == 4) HIPCK(hipMemcpyAsync(dc0, a.cbar_in, (size_t)p.batch * p.hidden * 4, hipMemcpyDeviceToDevice, C->cs));
+      return AMBPTT_OK;
+    }
     if (wide || sep32) {  // dL/dh_0 = zbar_0 W_h, dL/dc_0 = cbar_0
       ProdArgs pa{a.zbar_in, wide ? WhPk : WhT, nullptr, dh0, p.batch, p.hidden, L.G * p.hidden, L.ld_wht};
       ambptt_status s = timed(AMBPTT_K_OTHER, [&](hipEvent_t e0, hipEvent_t e1) {
@@ -1187,6 +1234,10 @@ ambptt_status prepare_inputs(ambptt_ctx* C, const void* W, const void* h0, const
       HIPCK(launch_pack_nt_bf16(W, GH, K1, K1, E.Wpk, C->cs));
       HIPCK(launch_pack_nt_bf16(E.WhT, p.hidden, GH, L.ld_wht, E.WhPk, C->cs));
     }
+  } else if (E.x3) {  // the split planes of W and of W_h^T
+    const int GH = L.G * p.hidden, K1 = p.input + p.hidden;
+    HIPCK(launch_pack_f32x3((const float*)W, GH, p.input, p.hidden, K1, false, E.Wx3, C->cs));
+    HIPCK(launch_pack_f32x3((const float*)W + p.input, p.hidden, 0, GH, K1, true, E.WhX3, C->cs));
   } else {
     HIPCK(launch_transpose_wh((const float*)W, (float*)E.WhT, L.G * p.hidden, p.input, p.hidden, L.ld_wht, C->cs));
   }

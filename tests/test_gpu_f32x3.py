@@ -1,0 +1,80 @@
+"""The large-batch fp32 kernels on the bf16 matrix cores (operands split in
+three bf16 parts), at sizes ragged against their tiles and 32-wide stages: row
+tiles of 256 and 128, units past the last tile, an input that ends inside a
+stage, no input at all.  Each run is compared with the oracle and, bit for
+bit, across schedules, and must be no further from the oracle than the fp32
+MFMA kernels on the same inputs (within the spread of two summation orders:
+a factor of 1.5)."""
+import numpy as np
+import pytest
+
+import synth
+
+from gpu_util import TOL_F32, assert_bitwise, assert_close, device_inputs, inputs, rel_err, run_gpu, run_oracle, say
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("loss", "dW", "db", "dh0", "dc0")
+
+
+def _rms(got, want):
+    got, want = np.asarray(got, np.float64), np.asarray(want, np.float64)
+    return float(np.sqrt(np.mean((got - want) ** 2)) / np.sqrt(np.mean(want ** 2)))
+
+
+@pytest.mark.parametrize("cell,B,D,H,n", [
+    ("lstm", 256, 16, 1024, 5),    # 128-row tiles, whole; the input fills half a stage
+    ("lstm", 300, 48, 1040, 5),    # partial row tile, units past the last tile, input of one and a half stages
+    ("lstm", 1030, 32, 1248, 3),   # 256-row tiles, the last of 6 rows
+    ("rnn", 300, 0, 1040, 6),      # no input; one gate
+    ("rnn", 1100, 80, 272, 6),     # K below two stages per part
+])
+def test_against_oracle(cell, B, D, H, n):
+    wl = synth.get("lstm_h4096_t20000").with_(cell=cell, loss="mean_sq_all", batch=B, input=D, hidden=H, n_steps=n,
+                                              w_scale=H ** -0.5, h0_std=0.3, name=f"{cell}_f32x3")
+    host = inputs(wl)
+    dev = device_inputs(wl, *host)
+    want = run_oracle(wl, *host)
+    a = run_gpu(wl, dev, fast_slots=3, slow_slots=n, interval_min=2)
+    assert_close(a, want, TOL_F32)
+    assert_bitwise(a, run_gpu(wl, dev, fast_slots=n, slow_slots=0))   # store-all
+    assert_bitwise(a, run_gpu(wl, dev, fast_slots=2, slow_slots=0))   # plain Revolve
+    old = run_gpu(wl, dev, fast_slots=3, slow_slots=n, interval_min=2, opts={"lds_gemm": 2})
+    for k in KEYS:
+        if k in want and k != "loss":
+            e, e0 = _rms(a[k], want[k]), _rms(old[k], want[k])
+            say(k, f"{e:.2e} split, {e0:.2e} fp32 MFMA")
+            assert e <= 1.5 * e0 + 1e-7, k
+
+
+def test_tiny_gradients():
+    # dL/dh_0 about 1e-36: zbar's low parts would leave bf16's range unscaled
+    wl = synth.get("lstm_h4096_t20000").with_(cell="rnn", loss="half_sq_last", batch=256, input=16, hidden=1024,
+                                              n_steps=22, w_scale=0.0022, h0_std=0.3, name="rnn_f32x3_tiny")
+    host = inputs(wl)
+    dev = device_inputs(wl, *host)
+    want = run_oracle(wl, *host)
+    say("max |dh0|", float(np.max(np.abs(want["dh0"]))))
+    assert 1e-37 < np.max(np.abs(want["dh0"])) < 1e-30
+    a = run_gpu(wl, dev, fast_slots=22, slow_slots=0)
+    assert rel_err(a["dh0"], want["dh0"]) <= 1e-5
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3e38])
+def test_values_that_do_not_split(value):
+    # an infinite, NaN or huge input behaves as with the fp32 MFMA kernels
+    wl = synth.get("lstm_h4096_t20000").with_(loss="mean_sq_all", batch=270, input=16, hidden=1024, n_steps=3,
+                                              w_scale=1.0 / 32, name="lstm_f32x3_nonfinite")
+    x, W, b, x0 = inputs(wl)
+    x = x.copy()
+    x[1, 5, 3] = value
+    dev = device_inputs(wl, x, W, b, x0)
+    a = run_gpu(wl, dev, fast_slots=3, slow_slots=0)
+    o = run_gpu(wl, dev, fast_slots=3, slow_slots=0, opts={"lds_gemm": 2})
+    for k in KEYS:
+        u, v = np.asarray(a[k], np.float64), np.asarray(o[k], np.float64)
+        assert np.array_equal(np.isnan(u), np.isnan(v)), k
+        assert np.array_equal(np.isinf(u), np.isinf(v)), k
+        f = np.isfinite(u)
+        if f.any():
+            assert np.max(np.abs(u[f] - v[f])) <= 1e-4 * max(np.max(np.abs(v[f])), 1e-30), k
