@@ -347,8 +347,8 @@ ambptt_status ambptt_bind(ambptt_ctx* ctx, void* slot_pool, size_t pool_bytes,
  * product with its cell epilogue and the h-adjoint product on the bf16 matrix
  * cores, each fp32 operand split exactly into three bf16 parts and the six
  * products that fp32 can tell apart summed in fp32 (with "hadj_launch" and
- * "prod_split" 1; operands under 4 GiB); elsewhere, as with 2 and without
- * the split, on LDS-tiled fp32 MFMA kernels
+ * "prod_split" 1; operands under 4 GiB), and so every fp32 cell's
+ * weight-gradient windows; elsewhere, as with 2 and without the split, on LDS-tiled fp32 MFMA kernels
  * (128 x 128 and 64 x 64 tiles, two workgroups per CU) where they
  * have at least 256 tiles; 2 wherever their shape constraints hold; 0 never:
  * the direct-load kernels), "hadj_launch" (1,

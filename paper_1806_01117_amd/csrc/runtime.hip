@@ -950,7 +950,9 @@ struct Exec {
           AMBPTT_K_DW,
           [&](hipEvent_t e0, hipEvent_t e1) {
             return L.mlpv ? launch_mlpv_dw(grp, int(cnt), ws, e0, e1)
-                          : p.dtype == AMBPTT_BF16 ? launch_dw_bf16(d, ws, e0, e1) : launch_dw(d, ws, e0, e1);
+                   : p.dtype == AMBPTT_BF16 ? launch_dw_bf16(d, ws, e0, e1)
+                   : C->lds_gemm == 1 && dw_f32x3_fits(d) ? launch_dw_f32x3(d, ws, e0, e1)
+                                                           : launch_dw(d, ws, e0, e1);
           },
           ws);
       if (s != AMBPTT_OK) return s;

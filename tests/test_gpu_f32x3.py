@@ -47,6 +47,29 @@ def test_against_oracle(cell, B, D, H, n):
             assert e <= 1.5 * e0 + 1e-7, k
 
 
+@pytest.mark.parametrize("cell,B,D,H,n,window", [
+    ("rnn", 1, 16, 16, 5, 2),       # one row per step, one 16-column block
+    ("rnn", 3, 0, 48, 40, 16),      # no input; windows of 48 rows, the last one short
+    ("lstm", 20, 48, 80, 33, 8),    # columns past the last tile of both operands
+    ("lstm", 33, 144, 128, 9, 31),  # the input ends inside a column tile; one window of 297 rows
+])
+def test_weight_gradient_windows(cell, B, D, H, n, window):
+    # one launch per step: only the windows run on the bf16 matrix cores
+    wl = synth.get("lstm_h512_t1000").with_(cell=cell, loss="mean_sq_all", batch=B, input=D, hidden=H, n_steps=n,
+                                            w_scale=H ** -0.5, h0_std=0.3, name=f"{cell}_dw_f32x3")
+    host = inputs(wl)
+    dev = device_inputs(wl, *host)
+    want = run_oracle(wl, *host)
+    a = run_gpu(wl, dev, path=1, window=window, fast_slots=3, slow_slots=n, interval_min=2)
+    assert_close(a, want, TOL_F32)
+    assert_bitwise(a, run_gpu(wl, dev, path=1, window=window, fast_slots=n, slow_slots=0))
+    old = run_gpu(wl, dev, path=1, window=window, fast_slots=3, slow_slots=n, interval_min=2, opts={"lds_gemm": 2})
+    for k in ("dW", "db"):
+        e, e0 = _rms(a[k], want[k]), _rms(old[k], want[k])
+        say(k, f"{e:.2e} split, {e0:.2e} fp32 MFMA")
+        assert e <= 1.5 * e0 + 1e-7, k
+
+
 def test_tiny_gradients():
     # dL/dh_0 about 1e-36: zbar's low parts would leave bf16's range unscaled
     wl = synth.get("lstm_h4096_t20000").with_(cell="rnn", loss="half_sq_last", batch=256, input=16, hidden=1024,
