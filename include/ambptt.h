@@ -123,9 +123,12 @@ typedef struct {
 } ambptt_stats;
 
 /* Kernel classes of ambptt_stats.kernel_*: forward step, the resident
- * whole-pass kernel, adjoint step (gate recomputation and cell adjoint), the
+ * whole-pass kernel, adjoint step (gate recomputation and cell adjoint; a step
+ * whose forward evaluation came just before keeps its pre-activations in the
+ * workspace, and its adjoint forms them no second time), the
  * adjoint's own product launch on the wide-batch bf16 path and the fp32
- * large-batch path (hbar = zbar W_h, or the MLP's ybar + zbar W_{l+1}),
+ * large-batch path (hbar = zbar W_h, or the MLP's ybar + zbar W_{l+1}, which
+ * with kept pre-activations forms the whole adjoint of the layer),
  * weight-gradient window, and everything
  * else. */
 enum { AMBPTT_K_FWD = 0, AMBPTT_K_PASS = 1, AMBPTT_K_ADJ = 2, AMBPTT_K_HADJ = 3,

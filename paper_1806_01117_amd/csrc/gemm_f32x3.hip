@@ -188,92 +188,53 @@ struct Tile {
   }
 };
 
-// ---- gate product with the cell epilogue --------------------------------------
-// Tile: TM batch rows x TN gate columns = U = TN / G units of all G gates
-// (16-column block b of the tile: gate b / (U / 16)).  The finished tile goes
-// to LDS, and every thread then takes four consecutive units of a row: the
-// epilogue's global accesses are 16 bytes per lane.
-template <int G, int MODE, int TM, int TN, int WM, int WN>
-__global__ __launch_bounds__(64 * WM * WN) void cell_f32x3(StepArgs a) {
-  using T = Tile<TM, TN, WM, WN>;
-  constexpr int U = TN / G, UB = U / 16, LZ = TN + 4;
-  constexpr int LDS = 2 * T::STAGE > TM * LZ * 4 ? 2 * T::STAGE : TM * LZ * 4;
-  __shared__ __attribute__((aligned(16))) char lds[LDS];
-  __shared__ float red[T::NW];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;
-  const int r = lane & 15, q = lane >> 4;
-  const int B = a.B, D = a.D, H = a.H, K1 = D + H, GH = G * H;
-  const int mt = (B + TM - 1) / TM, nt = (H + U - 1) / U;
-  int tm, tn;
-  tile_of(blockIdx.x, mt, nt, &tm, &tn);
-  const int m0 = tm * TM, j0 = tn * U;
-  const int hb = H / 16;
-  // units past H (the last tile): the last 16 units again, unused
-  auto bblk = [&](int b) { return (b / UB) * hb + min(j0 / 16 + b % UB, hb - 1); };
-
-  f4 acc[T::MI][T::NI];
-#pragma unroll
-  for (int i = 0; i < T::MI; ++i)
-#pragma unroll
-    for (int j = 0; j < T::NI; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-  const int kb = stages(D) + stages(H);
-  T::template run<true, false>((const float*)a.x, (const float*)a.h, B, D, H, m0, (const char*)a.Wx3,
-                               unsigned(GH / 16) * unsigned(kb) * unsigned(kBlk), kb, 0, kb, bblk, lds, acc);
-  if (any_bad(acc)) {
-    const float* W = (const float*)a.W;
-    T::exact((const float*)a.x, (const float*)a.h, B, D, H, m0, 0, K1,
-             [&](int j, int k) {
-               return *(const f4*)(W + (size_t)(16 * bblk(wn * T::NI + j) + r) * K1 + k);
-             },
-             acc);
-  }
-  float* z = (float*)lds;
-#pragma unroll
-  for (int i = 0; i < T::MI; ++i)
-#pragma unroll
-    for (int j = 0; j < T::NI; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        z[((wm * T::MI + i) * 16 + 4 * q + v) * LZ + (wn * T::NI + j) * 16 + r] = acc[i][j][v];
-  __syncthreads();
-
+// ---- epilogue of the gate product ----------------------------------------------
+// Every thread takes four consecutive units of a row, so that the global
+// accesses are 16 bytes per lane; zget(g, row, j) gives the pre-activations
+// (bias included) of gate g, tile row `row`, units j .. j + 3.  Forward: the
+// cell update; adjoint: loss term (returned), seed, cell adjoint, zbar_t,
+// cbar_t and the copy of h_t.  Contractions are fixed by the source, so that
+// the kernels that share this give the same bits.
+template <int G, int MODE, int TM, int U, int NT, class Z>
+__device__ __forceinline__ float cell_epilogue(const StepArgs& a, int m0, int j0, Z zget) {
+#pragma clang fp contract(on)
   float lterm = 0.f;
   constexpr int TPR = U / 4;  // threads per row
+  const int B = a.B, H = a.H, GH = G * H, tid = threadIdx.x;
   const int j = j0 + 4 * (tid % TPR);
   if (j < H) {
-    f4 bias[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) bias[g] = *(const f4*)(a.bias + g * H + j);
 #pragma unroll 2
-    for (int row = tid / TPR; row < TM; row += T::NT / TPR) {
+    for (int row = tid / TPR; row < TM; row += NT / TPR) {
       const int m = m0 + row;
       if (m >= B) break;
       const size_t o = (size_t)m * H + j;
-      const float* zr = z + row * LZ + (j - j0);
+      f4 z[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) z[g] = zget(g, row, j);
       f4 h1, c1, tc, ig, fg, gg, og, cold;
       if (G == 4) {
-        const f4 z0 = *(const f4*)zr + bias[0], z1 = *(const f4*)(zr + U) + bias[G > 1 ? 1 : 0];
-        const f4 z2 = *(const f4*)(zr + 2 * U) + bias[G > 1 ? 2 : 0], z3 = *(const f4*)(zr + 3 * U) + bias[G > 1 ? 3 : 0];
         cold = *(const f4*)(a.c + o);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          ig[e] = sigm(z0[e]);
-          fg[e] = sigm(z1[e]);
-          gg[e] = tanhf(z2[e]);
-          og[e] = sigm(z3[e]);
+          ig[e] = sigm(z[0][e]);
+          fg[e] = sigm(z[1 % G][e]);
+          gg[e] = tanhf(z[2 % G][e]);
+          og[e] = sigm(z[3 % G][e]);
           c1[e] = fg[e] * cold[e] + ig[e] * gg[e];
           tc[e] = tanhf(c1[e]);
           h1[e] = og[e] * tc[e];
         }
       } else {
-        const f4 z0 = *(const f4*)zr + bias[0];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) h1[e] = tanhf(z0[e]);
+        for (int e = 0; e < 4; ++e) h1[e] = tanhf(z[0][e]);
       }
       if (MODE == kForward) {
         *(f4*)((float*)a.h_out + o) = h1;
         if (G == 4) *(f4*)(a.c_out + o) = c1;
+        if (a.zc_out) {
+#pragma unroll
+          for (int g = 0; g < G; ++g) *(f4*)(a.zc_out + (size_t)m * GH + g * H + j) = z[g];
+        }
         continue;
       }
       // adjoint: loss term of h_{t+1} and its seed dL/dh_{t+1}
@@ -325,16 +286,91 @@ __global__ __launch_bounds__(64 * WM * WN) void cell_f32x3(StepArgs a) {
       *(f4*)((float*)a.hwin_out + o) = *(const f4*)((const float*)a.h + o);
     }
   }
-  if (MODE == kAdjoint) {  // the waves' loss terms, summed in wave order
-    const float s = wave_sum(lterm);
-    if (lane == 0) red[wave] = s;
-    __syncthreads();
-    if (tid == 0) {
-      double t = 0.0;
-      for (int w = 0; w < T::NW; ++w) t += (double)red[w];
-      a.loss_acc[blockIdx.x] += t;
-    }
+  return lterm;
+}
+
+// the waves' loss terms, summed in wave order
+template <int NW>
+__device__ __forceinline__ void add_loss(const StepArgs& a, float lterm, float* red) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const float s = wave_sum(lterm);
+  if (lane == 0) red[wave] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    for (int w = 0; w < NW; ++w) t += (double)red[w];
+    a.loss_acc[blockIdx.x] += t;
   }
+}
+
+// ---- gate product with the cell epilogue --------------------------------------
+// Tile: TM batch rows x TN gate columns = U = TN / G units of all G gates
+// (16-column block b of the tile: gate b / (U / 16)).  The finished tile goes
+// to the epilogue through LDS.
+template <int G, int MODE, int TM, int TN, int WM, int WN>
+__global__ __launch_bounds__(64 * WM * WN) void cell_f32x3(StepArgs a) {
+  using T = Tile<TM, TN, WM, WN>;
+  constexpr int U = TN / G, UB = U / 16, LZ = TN + 4;
+  constexpr int LDS = 2 * T::STAGE > TM * LZ * 4 ? 2 * T::STAGE : TM * LZ * 4;
+  __shared__ __attribute__((aligned(16))) char lds[LDS];
+  __shared__ float red[T::NW];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int r = lane & 15, q = lane >> 4;
+  const int B = a.B, D = a.D, H = a.H, K1 = D + H, GH = G * H;
+  const int mt = (B + TM - 1) / TM, nt = (H + U - 1) / U;
+  int tm, tn;
+  tile_of(blockIdx.x, mt, nt, &tm, &tn);
+  const int m0 = tm * TM, j0 = tn * U;
+  const int hb = H / 16;
+  // units past H (the last tile): the last 16 units again, unused
+  auto bblk = [&](int b) { return (b / UB) * hb + min(j0 / 16 + b % UB, hb - 1); };
+
+  f4 acc[T::MI][T::NI];
+#pragma unroll
+  for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+    for (int j = 0; j < T::NI; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+  const int kb = stages(D) + stages(H);
+  T::template run<true, false>((const float*)a.x, (const float*)a.h, B, D, H, m0, (const char*)a.Wx3,
+                               unsigned(GH / 16) * unsigned(kb) * unsigned(kBlk), kb, 0, kb, bblk, lds, acc);
+  if (any_bad(acc)) {
+    const float* W = (const float*)a.W;
+    T::exact((const float*)a.x, (const float*)a.h, B, D, H, m0, 0, K1,
+             [&](int j, int k) {
+               return *(const f4*)(W + (size_t)(16 * bblk(wn * T::NI + j) + r) * K1 + k);
+             },
+             acc);
+  }
+  float* z = (float*)lds;
+#pragma unroll
+  for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+    for (int j = 0; j < T::NI; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        z[((wm * T::MI + i) * 16 + 4 * q + v) * LZ + (wn * T::NI + j) * 16 + r] = acc[i][j][v];
+  __syncthreads();
+
+  const float lterm = cell_epilogue<G, MODE, TM, U, T::NT>(a, m0, j0, [&](int g, int row, int j) {
+    return *(const f4*)(z + row * LZ + g * U + (j - j0)) + *(const f4*)(a.bias + g * H + j);
+  });
+  if (MODE == kAdjoint) add_loss<T::NW>(a, lterm, red);
+}
+
+// The adjoint of a step whose pre-activations are kept: the same tiles and
+// the same threads for the same elements (so the same loss sums), without the
+// product.  Bound by HBM: 5 [B][4 H] or so arrays of the LSTM in and out.
+template <int G, int TM, int TN, int WM, int WN>
+__global__ __launch_bounds__(64 * WM * WN) void cell_back_f32x3(StepArgs a) {
+  constexpr int U = TN / G;
+  __shared__ float red[WM * WN];
+  int tm, tn;
+  tile_of(blockIdx.x, (a.B + TM - 1) / TM, (a.H + U - 1) / U, &tm, &tn);
+  const float lterm = cell_epilogue<G, kAdjoint, TM, U, 64 * WM * WN>(a, tm * TM, tn * U, [&](int g, int row, int j) {
+    return *(const f4*)(a.zc_in + (size_t)(tm * TM + row) * (G * a.H) + g * a.H + j);
+  });
+  add_loss<WM * WN>(a, lterm, red);
 }
 
 // ---- h-adjoint product: out = zbar W_h, the reduction split --------------------
@@ -461,7 +497,12 @@ hipError_t cell_launch(const StepArgs& a, hipStream_t s, hipEvent_t e0, hipEvent
   // two workgroups to a CU (300 x 4096 x 1120: 64 tiles of 256 x 128, 192 of
   // 128 x 64)
   if (tiles(256, 128) >= 192) {
-    hipExtLaunchKernelGGL((cell_f32x3<G, MODE, 256, 128, 4, 2>), dim3(tiles(256, 128)), dim3(512), 0, s, e0, e1, 0, a);
+    if (MODE == kAdjoint && a.zc_in)
+      hipExtLaunchKernelGGL((cell_back_f32x3<G, 256, 128, 4, 2>), dim3(tiles(256, 128)), dim3(512), 0, s, e0, e1, 0, a);
+    else
+      hipExtLaunchKernelGGL((cell_f32x3<G, MODE, 256, 128, 4, 2>), dim3(tiles(256, 128)), dim3(512), 0, s, e0, e1, 0, a);
+  } else if (MODE == kAdjoint && a.zc_in) {
+    hipExtLaunchKernelGGL((cell_back_f32x3<G, 128, 64, 4, 1>), dim3(tiles(128, 64)), dim3(256), 0, s, e0, e1, 0, a);
   } else {
     hipExtLaunchKernelGGL((cell_f32x3<G, MODE, 128, 64, 4, 1>), dim3(tiles(128, 64)), dim3(256), 0, s, e0, e1, 0, a);
   }

@@ -42,6 +42,11 @@ struct StepArgs {
   float inv_bh;          // 1 / (B H)
   int ld_wht = 0;        // row stride of WhT in elements (0: G*H)
   int hbar_parts = 1;    // hbar_in holds this many [B][H] partial sums, added in order
+  // pre-activations of the step (bias included), fp32 [B][G*H]: written by a
+  // forward step that the step's adjoint follows, and read by that adjoint in
+  // place of its gate product (null: not kept)
+  float* zc_out = nullptr;
+  const float* zc_in = nullptr;
   const void* Wx3 = nullptr;  // the split planes of W (launch_pack_f32x3), for the cell on bf16 matrix cores
 };
 
@@ -74,6 +79,8 @@ struct MlpArgs {
   float* dy0;
   int B, w, loss, first;
   float inv_bw;
+  float* zc_out = nullptr;       // pre-activations z_l (bias included) fp32 [B][w], as in StepArgs
+  const float* zc_in = nullptr;
 };
 
 // One product of the wide-batch adjoint: out = add (if given) + A Bm, A [M][K]
@@ -91,8 +98,9 @@ struct ProdArgs {
 
 // One launch of the MLP whose layers change width (mlp_f32.hip):
 //   kForward  out = relu(A W^T + bias)                  A [M][K], W [N][K]
-//   kAdjoint  zbar_out = (nn_in + dL/dy') * 1[A W^T + bias > 0], y' = relu(...),
-//             its loss term added to loss_acc[workgroup]
+//   kAdjoint  zbar_out = (u + dL/dy') * 1[y' > 0], y' = relu(A W^T + bias), its
+//             loss term added to loss_acc[workgroup].  The last layer: y' is
+//             formed and u = 0; the others: u = A2 W2, and y' is read (ynext)
 //   kFinal    out = A W (+ add)                          A [M][K], W [K][N]
 // M >= 1 rows; N and K multiples of 16.  inv = 1 / (M N) of the layer's output.
 struct MlpvArgs {
@@ -101,11 +109,11 @@ struct MlpvArgs {
   const float* bias;
   const float* add;
   float* out;
-  const float* nn_in;  // adjoint: zbar_{l+1} W_{l+1} [M][N], NULL for the last layer
   float* zbar_out;
   float* ywin_out;     // adjoint: a copy of A (y_l) for the weight gradient, NULL for none
-  const float* A2;     // adjoint in one launch: zbar_{l+1} [M][K2], NULL: nn_in (or nothing) instead
+  const float* A2;     // adjoint: zbar_{l+1} [M][K2], NULL for the last layer
   const float* W2;     // W_{l+1} [K2][N]
+  const float* ynext;  // adjoint with A2: y_{l+1} [M][N]
   double* loss_acc;
   int M, N, K, K2;
   int loss, last;
@@ -240,6 +248,8 @@ hipError_t launch_prod_nn(const ProdArgs& a, hipStream_t s, hipEvent_t e0 = null
 int mlp_wide_tiles(int B, int w);
 hipError_t launch_mlp_wide(int mode, const MlpArgs& a, hipStream_t s, hipEvent_t e0 = nullptr,
                            hipEvent_t e1 = nullptr);
+// the adjoint of a layer whose z_l is kept (a.zc_in), its product with W_{l+1} in the same launch
+hipError_t launch_mlp_back_wide(const MlpArgs& a, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 hipError_t launch_dw_bf16(const DwArgs& a, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 // The MLP of layers of different widths: workgroups of one launch on M x N,
 // and the launch (mode kForward, kAdjoint, or kFinal for the NN product).

@@ -10,7 +10,10 @@
 //   gradient  dW_l = zbar_l^T y_l,  db_l = column sums of zbar_l (mlpv_dw, a window of layers per launch)
 //
 // One launch per step: the forward, the NN product alone (dL/dy_0), and the
-// adjoint, which also forms u for its own tile.  A workgroup of 16 waves owns
+// adjoint.  Since y_{l+1} = relu(z_l), y_{l+1} > 0 exactly where z_l > 0, so
+// the adjoint of layer l takes its mask (and the loss its value) from the copy
+// of y_{l+1} that the adjoint of layer l + 1 left for its weight gradient, and
+// forms only u; the last layer's adjoint forms z_l.  A workgroup of 16 waves owns
 // 32 x 32 outputs, its waves split the reduction, and the partial tiles meet
 // in LDS in wave order (deterministic).  Widths are multiples of 16; a tile's
 // second column block may fall past N and then idles.  The loss terms of a
@@ -37,7 +40,7 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-enum { kMlpvFwd = 0, kMlpvAdj = 1, kMlpvNN = 2, kMlpvAdjU = 3 };
+enum { kMlpvFwd = 0, kMlpvAdj = 1, kMlpvNN = 2, kMlpvBack = 3 };  // kMlpvAdj: the last layer
 
 constexpr int kVW = 16;  // waves per workgroup
 
@@ -121,26 +124,15 @@ struct TileProduct {
       }
     }
   }
-  // the whole product; with pre, group 0's loads were issued already into xa0, xb0
-  __device__ __forceinline__ void run(const MlpvTile& t, float (&bt)[16][36], float* ywin, f4 (&acc)[RT][2],
-                                      f4 (*xa0)[RT] = nullptr, f4 (*xb0)[2] = nullptr) const {
+  // the whole product
+  __device__ __forceinline__ void run(const MlpvTile& t, float (&bt)[16][36], float* ywin, f4 (&acc)[RT][2]) const {
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
     for (int g = 0; g < ngrp; ++g) {
       f4 xa[ND][RT], xb[ND][2];
-      if (g == 0 && xa0) {
-#pragma unroll
-        for (int u = 0; u < ND; ++u) {
-#pragma unroll
-          for (int i = 0; i < RT; ++i) xa[u][i] = xa0[u][i];
-#pragma unroll
-          for (int j = 0; j < 2; ++j) xb[u][j] = xb0[u][j];
-        }
-      } else {
-        load(t, g, xa, xb);
-      }
+      load(t, g, xa, xb);
       __builtin_amdgcn_sched_barrier(0);  // every load of the group issues before its first MFMA
       mma(t, g, xa, xb, bt, ywin, acc);
     }
@@ -171,14 +163,12 @@ __device__ __forceinline__ float tile_sum(const MlpvTile& t, float (&part)[kVW][
 // One launch per step.  A workgroup of 16 waves owns 16 RT rows x 32 columns
 // of the step's output (RT = 1 where 32-row tiles would leave the device
 // short of workgroups); its first 512 RT threads run the epilogue, 32
-// consecutive columns per half wave.  kMlpvAdjU runs the adjoint's two products in one launch:
-// first u = zbar_{l+1} W_{l+1} (NN, reduction over w_{l+2}, with ND2), then
-// z_l (NT, with ND), the LDS tiles reused in between.  Its u is summed in
-// the same order as the NN launch's.
-template <int MODE, int ND, int ND2, int RT>
+// consecutive columns per half wave.
+template <int MODE, int ND, int RT>
 __global__ __launch_bounds__(64 * kVW) void mlpv_gemm(MlpvArgs a) {
+  constexpr bool NN = MODE == kMlpvNN || MODE == kMlpvBack;
   __shared__ float part[kVW][32][36];  // partial tiles; rows of 36: the stores of a wave spread over the banks
-  __shared__ __attribute__((aligned(16))) float bt[(MODE == kMlpvNN || MODE == kMlpvAdjU) ? kVW : 1][16][36];
+  __shared__ __attribute__((aligned(16))) float bt[NN ? kVW : 1][16][36];
   __shared__ float lpart[kVW];
   MlpvTile t;
   t.tid = threadIdx.x;
@@ -189,33 +179,33 @@ __global__ __launch_bounds__(64 * kVW) void mlpv_gemm(MlpvArgs a) {
   t.m0 = blockIdx.x * 16 * RT;
   t.n0 = blockIdx.y * 32;
   const int M = a.M, N = a.N;
-  const bool adj = MODE == kMlpvAdj || MODE == kMlpvAdjU;
-  float u = 0.f;
-  const TileProduct<MODE == kMlpvNN, ND, RT> main(t, a.A, a.W, M, N, a.K);
+  const bool adj = MODE == kMlpvAdj || MODE == kMlpvBack;
+  const int m = t.m0 + (t.tid >> 5), n = t.n0 + (t.tid & 31);
+  const bool own = t.tid < 512 * RT && m < M && n < N;
   f4 acc[RT][2];
-  if (MODE == kMlpvAdjU) {
-    f4 acc2[RT][2];
-    TileProduct<true, ND2, RT>(t, a.A2, a.W2, M, N, a.K2).run(t, bt[t.wave], nullptr, acc2);
-    // the main product's first loads go out before the reduction of u
-    f4 xa0[ND][RT], xb0[ND][2];
-    main.load(t, 0, xa0, xb0);
-    u = tile_sum(t, part, acc2);
-    __syncthreads();  // part is written again below
-    main.run(t, bt[0], a.ywin_out, acc, xa0, xb0);
+  float y1 = 0.f;
+  if (MODE == kMlpvBack) {
+    // the weight gradient's copy of y_l, a slice per workgroup, and the mask
+    // go out before the product
+    if (a.ywin_out) {
+      const int n4 = M * (a.K / 4), step = int(gridDim.x * gridDim.y) * 64 * kVW;
+      for (int i = int(blockIdx.y * gridDim.x + blockIdx.x) * 64 * kVW + t.tid; i < n4; i += step)
+        ((f4*)a.ywin_out)[i] = ((const f4*)a.A)[i];
+    }
+    if (own) y1 = a.ynext[(size_t)m * N + n];
+    TileProduct<true, ND, RT>(t, a.A2, a.W2, M, N, a.K2).run(t, bt[t.wave], nullptr, acc);
   } else {
-    main.run(t, bt[MODE == kMlpvNN ? t.wave : 0], adj ? a.ywin_out : nullptr, acc);
+    TileProduct<NN, ND, RT>(t, a.A, a.W, M, N, a.K).run(t, bt[NN ? t.wave : 0], adj ? a.ywin_out : nullptr, acc);
   }
   const float sum = tile_sum(t, part, acc);
 
-  const int m = t.m0 + (t.tid >> 5), n = t.n0 + (t.tid & 31);
   float lterm = 0.f;
-  if (t.tid < 512 * RT && m < M && n < N) {
+  if (own) {
     const size_t o = (size_t)m * N + n;
     if (MODE == kMlpvNN) {
       a.out[o] = a.add ? a.add[o] + sum : sum;
     } else {
-      const float z = sum + a.bias[n];
-      const float y1 = fmaxf(z, 0.f);
+      if (MODE != kMlpvBack) y1 = fmaxf(sum + a.bias[n], 0.f);
       if (MODE == kMlpvFwd) {
         a.out[o] = y1;
       } else {
@@ -234,8 +224,8 @@ __global__ __launch_bounds__(64 * kVW) void mlpv_gemm(MlpvArgs a) {
             lterm = y1 * a.inv;
           }
         }
-        const float yb1 = (MODE == kMlpvAdjU ? u : a.nn_in ? a.nn_in[o] : 0.f) + sd;
-        a.zbar_out[o] = z > 0.f ? yb1 : 0.f;
+        const float yb1 = (MODE == kMlpvBack ? sum : 0.f) + sd;
+        a.zbar_out[o] = y1 > 0.f ? yb1 : 0.f;
       }
     }
   }
@@ -388,35 +378,30 @@ static int mlpv_nd(int K) { return std::min(4, std::max(1, (K / 16 + kVW - 1) / 
 // rows per tile: 32, or 16 where 32-row tiles give fewer workgroups than CUs
 static int mlpv_rows(int M, int N) { return ((M + 31) / 32) * ((N + 31) / 32) < 256 ? 16 : 32; }
 
-template <int MODE, int ND2, int RT>
+template <int MODE, int RT>
 static hipError_t launch_mlpv_rt(const MlpvArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   const dim3 grid((a.M + 16 * RT - 1) / (16 * RT), (a.N + 31) / 32), block(64 * kVW);
-  switch (mlpv_nd(a.K)) {
-    case 1: hipExtLaunchKernelGGL((mlpv_gemm<MODE, 1, ND2, RT>), grid, block, 0, s, e0, e1, 0, a); break;
-    case 2: hipExtLaunchKernelGGL((mlpv_gemm<MODE, 2, ND2, RT>), grid, block, 0, s, e0, e1, 0, a); break;
-    case 3: hipExtLaunchKernelGGL((mlpv_gemm<MODE, 3, ND2, RT>), grid, block, 0, s, e0, e1, 0, a); break;
-    default: hipExtLaunchKernelGGL((mlpv_gemm<MODE, 4, ND2, RT>), grid, block, 0, s, e0, e1, 0, a); break;
+  switch (mlpv_nd(MODE == kMlpvBack ? a.K2 : a.K)) {
+    case 1: hipExtLaunchKernelGGL((mlpv_gemm<MODE, 1, RT>), grid, block, 0, s, e0, e1, 0, a); break;
+    case 2: hipExtLaunchKernelGGL((mlpv_gemm<MODE, 2, RT>), grid, block, 0, s, e0, e1, 0, a); break;
+    case 3: hipExtLaunchKernelGGL((mlpv_gemm<MODE, 3, RT>), grid, block, 0, s, e0, e1, 0, a); break;
+    default: hipExtLaunchKernelGGL((mlpv_gemm<MODE, 4, RT>), grid, block, 0, s, e0, e1, 0, a); break;
   }
   return hipGetLastError();
 }
 
-template <int MODE, int ND2>
-static hipError_t launch_mlpv_nd(const MlpvArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  return mlpv_rows(a.M, a.N) == 16 ? launch_mlpv_rt<MODE, ND2, 1>(a, s, e0, e1) : launch_mlpv_rt<MODE, ND2, 2>(a, s, e0, e1);
+template <int MODE>
+static hipError_t launch_mlpv_mode(const MlpvArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  return mlpv_rows(a.M, a.N) == 16 ? launch_mlpv_rt<MODE, 1>(a, s, e0, e1) : launch_mlpv_rt<MODE, 2>(a, s, e0, e1);
 }
 
 hipError_t launch_mlpv(int mode, const MlpvArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (a.M < 1 || a.N < 16 || a.K < 16 || a.N % 16 || a.K % 16) return hipErrorInvalidValue;
-  if (mode == kForward) return launch_mlpv_nd<kMlpvFwd, 1>(a, s, e0, e1);
-  if (mode == kFinal) return launch_mlpv_nd<kMlpvNN, 1>(a, s, e0, e1);
-  if (!a.A2) return launch_mlpv_nd<kMlpvAdj, 1>(a, s, e0, e1);
-  if (a.K2 < 16 || a.K2 % 16 || !a.W2 || a.nn_in) return hipErrorInvalidValue;
-  switch (mlpv_nd(a.K2)) {
-    case 1: return launch_mlpv_nd<kMlpvAdjU, 1>(a, s, e0, e1);
-    case 2: return launch_mlpv_nd<kMlpvAdjU, 2>(a, s, e0, e1);
-    case 3: return launch_mlpv_nd<kMlpvAdjU, 3>(a, s, e0, e1);
-    default: return launch_mlpv_nd<kMlpvAdjU, 4>(a, s, e0, e1);
-  }
+  if (mode == kForward) return launch_mlpv_mode<kMlpvFwd>(a, s, e0, e1);
+  if (mode == kFinal) return launch_mlpv_mode<kMlpvNN>(a, s, e0, e1);
+  if (!a.A2) return launch_mlpv_mode<kMlpvAdj>(a, s, e0, e1);
+  if (a.K2 < 16 || a.K2 % 16 || !a.W2 || !a.ynext) return hipErrorInvalidValue;
+  return launch_mlpv_mode<kMlpvBack>(a, s, e0, e1);
 }
 
 }  // namespace ambptt

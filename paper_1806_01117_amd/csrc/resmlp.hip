@@ -59,7 +59,8 @@ struct Mop<__bf16> {
 constexpr int kWaves = 8;
 constexpr int kU = 4;
 
-template <class T, int MODE>
+// CACHED (adjoint): z_l is kept (a.zc_in) and not formed again.
+template <class T, int MODE, bool CACHED = false>
 __global__ __launch_bounds__(64 * kWaves) void resmlp_step(MlpArgs a) {
   using V = typename Mop<T>::V;
   constexpr int CW = Mop<T>::CW, LE = Mop<T>::LE;
@@ -82,7 +83,7 @@ __global__ __launch_bounds__(64 * kWaves) void resmlp_step(MlpArgs a) {
   const int k0c = (nch * wave) / kWaves, k1c = (nch * (wave + 1)) / kWaves;
 
   // z_l = y_l W_l^T for this tile (forward and adjoint)
-  if (MODE != kFinal) {
+  if (MODE != kFinal && !CACHED) {
     f4 acc = {0.f, 0.f, 0.f, 0.f};
     const T* yr = (const T*)a.y + (size_t)row * w;
     const T* wr = (const T*)a.W + (size_t)(c0 + r) * w;
@@ -137,6 +138,7 @@ __global__ __launch_bounds__(64 * kWaves) void resmlp_step(MlpArgs a) {
   // epilogue: thread (m, c), 16 x 16 per workgroup
   float lterm = 0.f;
   if (tid < 256) {
+#pragma clang fp contract(on)  // the same bits with and without the product
     const int ml = tid >> 4, cl = tid & 15;
     const int m = m0 + ml, c = c0 + cl;
     if (m < B) {
@@ -150,9 +152,14 @@ __global__ __launch_bounds__(64 * kWaves) void resmlp_step(MlpArgs a) {
         a.dy0[o] = a.ybar_in[o] + nn;
       } else {
         float z = 0.f;
+        if (CACHED) {
+          z = a.zc_in[o];
+        } else {
 #pragma unroll
-        for (int v = 0; v < kWaves; ++v) z += zs[v][ml][cl];
-        z += a.bias[c];
+          for (int v = 0; v < kWaves; ++v) z += zs[v][ml][cl];
+          z += a.bias[c];
+          if (MODE == kForward && a.zc_out) a.zc_out[o] = z;
+        }
         const float yv = Mop<T>::load(((const T*)a.y)[o]);
         const float y1 = yv + fmaxf(z, 0.f);
         const T y1s = Mop<T>::store(y1);
@@ -212,13 +219,15 @@ void resmlp_grid(int B, int w, dim3* grid, dim3* block) {
 hipError_t launch_resmlp(int bf16, int mode, const MlpArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   dim3 grid, block;
   resmlp_grid(a.B, a.w, &grid, &block);
-#define AMB_M(T_, M_) hipExtLaunchKernelGGL((resmlp_step<T_, M_>), grid, block, 0, s, e0, e1, 0, a)
+#define AMB_M(T_, ...) hipExtLaunchKernelGGL((resmlp_step<T_, __VA_ARGS__>), grid, block, 0, s, e0, e1, 0, a)
   if (bf16) {
     if (mode == kForward) AMB_M(__bf16, kForward);
+    else if (mode == kAdjoint && a.zc_in) AMB_M(__bf16, kAdjoint, true);
     else if (mode == kAdjoint) AMB_M(__bf16, kAdjoint);
     else AMB_M(__bf16, kFinal);
   } else {
     if (mode == kForward) AMB_M(float, kForward);
+    else if (mode == kAdjoint && a.zc_in) AMB_M(float, kAdjoint, true);
     else if (mode == kAdjoint) AMB_M(float, kAdjoint);
     else AMB_M(float, kFinal);
   }

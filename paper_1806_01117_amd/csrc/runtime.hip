@@ -69,6 +69,10 @@ struct Layout {
   // large-batch fp32 cell on the bf16 matrix cores: W's and W_h^T's split planes
   bool x3 = false;
   size_t off_wx3 = 0, off_whx3 = 0;
+  // ring of zc_slots steps' pre-activations (fp32): a forward step whose
+  // adjoint comes next leaves them for it
+  int zc_slots = 0;
+  size_t off_zc = 0, zc_bytes = 0;
   int ld_wht = 0;        // row stride of WhT in elements
   size_t off_loss = 0, off_lossout = 0, total = 0;
   int loss_slots = 0;
@@ -254,6 +258,19 @@ Layout make_layout(const ambptt_problem* p, int window) {
       L.off_wx3 = o; o += align_up(f32x3_bytes(int(GH), p->input, p->hidden));
       L.off_whx3 = o; o += align_up(f32x3_bytes(p->hidden, 0, int(GH)));
     }
+  }
+  // The paths whose adjoint can take kept pre-activations: all but the
+  // fp32 MFMA kernels of large batches.  16 steps (an interval of the
+  // two-level schedules is rarely longer, and a longer reversal's innermost
+  // parts fit), at most 512 MiB of them; a workspace that fits
+  // ambptt_run_noalloc's scratch array stays within it.
+  if (L.x3 || L.wide || L.small || L.mlp) {
+    L.zc_bytes = align_up(BH * size_t(L.G) * 4);
+    size_t room = size_t(512) << 20;
+    if (o <= kScratchBytes) room = std::min(room, kScratchBytes - o);
+    L.zc_slots = int(std::min<size_t>({size_t(16), size_t(p->n_steps), room / L.zc_bytes}));
+    L.off_zc = o;
+    o += size_t(L.zc_slots) * L.zc_bytes;
   }
   L.total = o;
   return L;
@@ -559,6 +576,13 @@ struct Exec {
   void* Wpk = nullptr;   // wide bf16 cell: W in fragment order (the gate products)
   void* WhPk = nullptr;  // ... and W_h^T (the h-adjoint products)
   ambptt_stats st{};
+  // kept pre-activations: zc_t[k] is the step whose pre-activations ring slot
+  // k holds (-1: none); keep[i]: forward evaluation i of the actions being run
+  // is the last of its step before the step's adjoint, and a slot is free
+  // from it to there
+  std::vector<int64_t> zc_t;
+  std::vector<char> keep;
+  size_t keep_i = 0;
   char* cur = nullptr;
   int cur_slot = -1;  // slot index the live state aliases, or -1
   int cur_live = -1;  // live buffer index, or -1
@@ -591,6 +615,7 @@ struct Exec {
     slot_off.resize(C->pend.size());
     for (size_t k = 0; k < slot_off.size(); ++k) slot_off[k] = k * L.stride;
     WhT = C->ws + L.off_wht;
+    zc_t.assign(size_t(L.zc_slots), -1);
     wide = L.wide && C->wide_opt;
     sep32 = L.hsep && C->hadj_launch;
     if (L.hsep) {
@@ -748,6 +773,46 @@ struct Exec {
                    : launch_step(L.G, mode, L.cfg, a, C->cs, e0, e1);
   }
 
+  // Which forward evaluations of acts[from ..] keep their pre-activations:
+  // backwards from each step's adjoint to the step's last evaluation before
+  // it, the step takes ring slot t % slots; where two steps want the same
+  // slot at once, the one whose adjoint comes first has it.
+  void plan_keep(const std::vector<Action>& acts, size_t from) {
+    keep.clear();
+    keep_i = 0;
+    if (zc_t.empty() || (L.hsep && !x3)) return;
+    size_t evals = 0;
+    for (size_t i = from; i < acts.size(); ++i)
+      if (acts[i].op == Op::Advance) evals += size_t(acts[i].b - acts[i].a);
+    keep.assign(evals, 0);
+    const int64_t slots = int64_t(zc_t.size());
+    std::vector<int64_t> want(zc_t.size(), -1);
+    for (size_t i = acts.size(); i-- > from;) {
+      const Action& A = acts[i];
+      if (A.op == Op::Youturn) want[size_t(A.a % slots)] = A.a;
+      if (A.op != Op::Advance) continue;
+      for (int64_t t = A.b; t-- > A.a;) {
+        --evals;
+        if (want[size_t(t % slots)] != t) continue;
+        keep[evals] = 1;
+        want[size_t(t % slots)] = -1;
+      }
+    }
+  }
+  float* zc_at(int64_t t) const {
+    return (float*)(C->ws + L.off_zc + size_t(t % int64_t(zc_t.size())) * L.zc_bytes);
+  }
+  // where this forward evaluation of step t leaves its pre-activations (null: nowhere)
+  float* zc_keep(int64_t t) {
+    if (keep_i >= keep.size() || !keep[keep_i++]) return nullptr;
+    zc_t[size_t(t % int64_t(zc_t.size()))] = t;
+    return zc_at(t);
+  }
+  // step t's pre-activations, if they are kept
+  const float* zc_kept(int64_t t) const {
+    return !zc_t.empty() && zc_t[size_t(t % int64_t(zc_t.size()))] == t ? zc_at(t) : nullptr;
+  }
+
   // one forward step: state at `src` -> `dst`
   // residual MLP: layer t's weights and bias
   const void* W_of(int64_t t) const {
@@ -790,6 +855,7 @@ struct Exec {
       MlpArgs a = mlp_args(t);
       a.y = src;
       a.y_out = dst;
+      a.zc_out = zc_keep(t);
       return timed(AMBPTT_K_FWD, [&](hipEvent_t e0, hipEvent_t e1) {
         return wide ? launch_mlp_wide(kForward, a, C->cs, e0, e1)
                     : launch_resmlp(p.dtype == AMBPTT_BF16, kForward, a, C->cs, e0, e1);
@@ -801,6 +867,7 @@ struct Exec {
     a.c = L.G == 4 ? cpart(src) : nullptr;
     a.h_out = hpart(dst);
     a.c_out = L.G == 4 ? cpart(dst) : nullptr;
+    a.zc_out = zc_keep(t);
     return timed(AMBPTT_K_FWD, [&](hipEvent_t e0, hipEvent_t e1) { return launch(kForward, a, e0, e1); });
   }
 
@@ -845,6 +912,7 @@ struct Exec {
         a.A2 = (const float*)zbar_at(t + 1);
         a.W2 = (const float*)W + C->woff[size_t(t) + 1];
         a.K2 = C->widths[size_t(t) + 2];
+        a.ynext = (const float*)hwin_at(t + 1);  // y_{t+1}, as the adjoint of layer t + 1 left it
       }
       s = timed(AMBPTT_K_ADJ, [&](hipEvent_t e0, hipEvent_t e1) { return launch_mlpv(kAdjoint, a, C->cs, e0, e1); });
       if (s != AMBPTT_OK) return s;
@@ -859,7 +927,10 @@ struct Exec {
       a.ybar_out = cbar(t);
       a.ywin_out = hwin_at(t);
       a.loss_acc = (double*)(C->ws + L.off_loss);
-      if (wide) {
+      a.zc_in = first ? nullptr : zc_kept(t);
+      if (wide && a.zc_in) {  // the product and the layer's adjoint in one launch
+        s = timed(AMBPTT_K_HADJ, [&](hipEvent_t e0, hipEvent_t e1) { return launch_mlp_back_wide(a, C->cs, e0, e1); });
+      } else if (wide) {
         if (!first) {  // ybar_{l+2} + zbar_{l+1} W_{l+1}
           ProdArgs pa{a.zbar_in, a.Wn, a.ybar_in, hbuf, p.batch, p.hidden, p.hidden};
           s = timed(AMBPTT_K_HADJ, [&](hipEvent_t e0, hipEvent_t e1) { return launch_prod_nn(pa, C->cs, e0, e1); });
@@ -885,6 +956,7 @@ struct Exec {
       a.cbar_out = cbar(t);
       a.hwin_out = hwin_at(t);
       a.loss_acc = (double*)(C->ws + L.off_loss);
+      a.zc_in = first ? nullptr : zc_kept(t);
       if ((wide || sep32) && !first) {  // hbar_{t+1} = zbar_{t+1} W_h
         ProdArgs pa{a.zbar_in, wide ? WhPk : WhT, nullptr, hbuf, p.batch, p.hidden, L.G * p.hidden, L.ld_wht};
         if (x3) pa = x3_prod(a.zbar_in, hbuf);
@@ -1110,6 +1182,7 @@ struct Exec {
 
   ambptt_status run_acts(const std::vector<Action>& acts, size_t from, float* dW, float* db) {
     ambptt_status s;
+    plan_keep(acts, from);
     for (size_t i = from; i < acts.size(); ++i) {
       const Action& A = acts[i];
       want_tail = copy_follows(acts, i + 1);

@@ -117,7 +117,9 @@ __device__ __forceinline__ void chunks(int c0, int c1, f4 (&acc)[NB], LA la, LB 
   }
 }
 
-template <class T, int G, int MODE>
+// CACHED (adjoint): the step's pre-activations are kept (a.zc_in) and its
+// gate product is not formed again.
+template <class T, int G, int MODE, bool CACHED = false>
 __global__ __launch_bounds__(64 * kWaves) void step_small(StepArgs a) {
   using V = typename Op<T>::V;
   constexpr int CW = Op<T>::CW;
@@ -141,10 +143,10 @@ __global__ __launch_bounds__(64 * kWaves) void step_small(StepArgs a) {
   const int wg_slot = w;   // loss accumulator of this tile
   const int row = min(m0 + r, B - 1);  // rows >= B: clamped loads, results dropped
 
-  __shared__ float zs[kWaves][16][NC + 1];
+  __shared__ float zs[CACHED ? 1 : kWaves][16][NC + 1];
   __shared__ float hs[kWaves][16][17];
 
-  if (MODE != kFinal) {
+  if (MODE != kFinal && !CACHED) {
     f4 acc[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[nb] = f4{0.f, 0.f, 0.f, 0.f};
@@ -187,6 +189,7 @@ __global__ __launch_bounds__(64 * kWaves) void step_small(StepArgs a) {
   // epilogue: thread (m, u) for m < 16, u < U
   float lterm = 0.f;
   if (tid < 16 * U) {
+#pragma clang fp contract(on)  // the same bits with and without the gate product
     const int ml = tid / U, u = tid % U;
     const int m = m0 + ml, j = j0 + u;
     if (m < B) {
@@ -203,10 +206,15 @@ __global__ __launch_bounds__(64 * kWaves) void step_small(StepArgs a) {
         float z[G];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-          float s = 0.f;
+          if (CACHED) {
+            z[g] = a.zc_in[(size_t)m * GH + g * H + j];
+          } else {
+            float s = 0.f;
 #pragma unroll
-          for (int w = 0; w < kWaves; ++w) s += zs[w][ml][g * U + u];
-          z[g] = s + a.bias[g * H + j];
+            for (int w = 0; w < kWaves; ++w) s += zs[w][ml][g * U + u];
+            z[g] = s + a.bias[g * H + j];
+            if (MODE == kForward && a.zc_out) a.zc_out[(size_t)m * GH + g * H + j] = z[g];
+          }
         }
         float h1, c1 = 0.f, tc = 0.f, ig = 0.f, fg = 0.f, gg = 0.f, og = 0.f, cold = 0.f;
         if (G == 4) {
@@ -287,14 +295,16 @@ hipError_t launch_step_small(int G, int bf16, int mode, const StepArgs& a, hipSt
                              hipEvent_t e1) {
   dim3 grid, block;
   step_small_grid(G, a.B, a.H, &grid, &block);
-#define AMB_L(T_, G_, M_) hipExtLaunchKernelGGL((step_small<T_, G_, M_>), grid, block, 0, s, e0, e1, 0, a)
+#define AMB_L(T_, G_, ...) hipExtLaunchKernelGGL((step_small<T_, G_, __VA_ARGS__>), grid, block, 0, s, e0, e1, 0, a)
 #define AMB_T(T_)                                   \
   if (G == 4) {                                     \
     if (mode == kForward) AMB_L(T_, 4, kForward);   \
+    else if (mode == kAdjoint && a.zc_in) AMB_L(T_, 4, kAdjoint, true); \
     else if (mode == kAdjoint) AMB_L(T_, 4, kAdjoint); \
     else AMB_L(T_, 4, kFinal);                      \
   } else {                                          \
     if (mode == kForward) AMB_L(T_, 1, kForward);   \
+    else if (mode == kAdjoint && a.zc_in) AMB_L(T_, 1, kAdjoint, true); \
     else if (mode == kAdjoint) AMB_L(T_, 1, kAdjoint); \
     else AMB_L(T_, 1, kFinal);                      \
   }

@@ -277,7 +277,10 @@ constexpr int lds_bytes() {
 // step t): with hbar_{t+1} from the product launch before it (absent for the
 // first turn) it forms zbar_t, cbar_t, the loss term and the copy of h_t for
 // the weight-gradient window.
-template <int G, int MODE, int NW = kWaves, int S = 2>
+// CACHED (adjoint): the pre-activations are kept (a.zc_in) and the gate
+// product is not formed again; the same tiles and threads take the same
+// elements.
+template <int G, int MODE, bool CACHED = false, int NW = kWaves, int S = 2>
 __global__ __launch_bounds__(64 * NW) void cell_wide(StepArgs a) {
   constexpr int RT = 4, NB = 4, TM = 64;
   constexpr int UN = 64 / G;  // hidden units of the tile
@@ -289,9 +292,9 @@ __global__ __launch_bounds__(64 * NW) void cell_wide(StepArgs a) {
   if (w >= ntile) return;  // grid padding (the whole workgroup leaves together)
   const int m0 = (w % mg) * TM, j0 = (w / mg) * UN;
 
-  __shared__ __attribute__((aligned(16))) char lds[lds_bytes<RT, NB, SCR, NW>()];
+  __shared__ __attribute__((aligned(16))) char lds[CACHED ? 16 : lds_bytes<RT, NB, SCR, NW>()];
   float* ps = (float*)lds;
-  {
+  if (!CACHED) {
     f4 acc[RT][NB];
 #pragma unroll
     for (int i = 0; i < RT; ++i)
@@ -318,13 +321,22 @@ __global__ __launch_bounds__(64 * NW) void cell_wide(StepArgs a) {
   // epilogue: pair (row ml, unit u), consecutive threads on consecutive units
   float lterm = 0.f;
   for (int pi = tid; pi < TM * UN; pi += 64 * NW) {
+#pragma clang fp contract(on)  // the same bits with and without the gate product
     const int ml = pi / UN, u = pi % UN;
     const int m = m0 + ml, j = j0 + u;
     if (m >= B) continue;
     const int o = m * H + j;
     float z[G];
 #pragma unroll
-    for (int g = 0; g < G; ++g) z[g] = sum_partials<RT, NB, NW>(ps, ml, g * UN + u) + a.bias[g * H + j];
+    for (int g = 0; g < G; ++g) {
+      const size_t zo = (size_t)m * GH + g * H + j;
+      if (CACHED) {
+        z[g] = a.zc_in[zo];
+      } else {
+        z[g] = sum_partials<RT, NB, NW>(ps, ml, g * UN + u) + a.bias[g * H + j];
+        if (MODE == kForward && a.zc_out) a.zc_out[zo] = z[g];
+      }
+    }
     float h1, c1 = 0.f, tc = 0.f, ig = 0.f, fg = 0.f, gg = 0.f, og = 0.f, cold = 0.f;
     if (G == 4) {
       ig = sigm(z[0]);
@@ -422,19 +434,16 @@ __device__ __forceinline__ bf16x8 nn_frag(const char* bt, int kb, int nb) {
 //     loaded (rows k of 128 bytes) and come back as fragments through
 //     gfx950's transposing LDS read, so no transposed copy of the weights
 //     is kept.
-template <int RT, int NB, bool NN, int NW = kWaves, int S = NN ? 2 : (RT * NB >= 4 ? 3 : 4)>
-__global__ __launch_bounds__(64 * NW) void prod_wide(ProdArgs a) {
-  constexpr int TM = 16 * RT, TN = 16 * NB;
-  constexpr int SCR = NN ? RT * kSlot + 64 * 128 : (RT + NB) * kSlot;
-  static_assert(!NN || TN == 64, "the NN product takes 64-column tiles");
+template <int RT, bool NN, int NB>
+constexpr int prod_scr() { return NN ? RT * kSlot + 64 * 128 : (RT + NB) * kSlot; }
+
+// the tile's partial sums in LDS (ready after the barrier that ends it)
+template <int RT, int NB, bool NN, int NW, int S>
+__device__ __forceinline__ void prod_tile(const ProdArgs& a, int m0, int n0, char* lds) {
+  constexpr int SCR = prod_scr<RT, NN, NB>();
+  static_assert(!NN || 16 * NB == 64, "the NN product takes 64-column tiles");
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int M = a.M, N = a.N, K = a.K;
-  const int mg = (M + TM - 1) / TM, ntile = mg * (N / TN);
-  const int w = tile_of(ntile);
-  if (w >= ntile) return;
-  const int m0 = (w % mg) * TM, n0 = (w / mg) * TN;
-
-  __shared__ __attribute__((aligned(16))) char lds[lds_bytes<RT, NB, SCR, NW>()];
   f4 acc[RT][NB];
 #pragma unroll
   for (int i = 0; i < RT; ++i)
@@ -497,9 +506,21 @@ __global__ __launch_bounds__(64 * NW) void prod_wide(ProdArgs a) {
         });
   }
   __syncthreads();  // every wave has left its scratch
-  float* ps = (float*)lds;
-  put_partials<RT, NB>(ps, wave, acc);
+  put_partials<RT, NB>((float*)lds, wave, acc);
   __syncthreads();
+}
+
+template <int RT, int NB, bool NN, int NW = kWaves, int S = NN ? 2 : (RT * NB >= 4 ? 3 : 4)>
+__global__ __launch_bounds__(64 * NW) void prod_wide(ProdArgs a) {
+  constexpr int TM = 16 * RT, TN = 16 * NB;
+  const int tid = threadIdx.x, M = a.M, N = a.N;
+  const int mg = (M + TM - 1) / TM, ntile = mg * (N / TN);
+  const int w = tile_of(ntile);
+  if (w >= ntile) return;
+  const int m0 = (w % mg) * TM, n0 = (w / mg) * TN;
+  __shared__ __attribute__((aligned(16))) char lds[lds_bytes<RT, NB, prod_scr<RT, NN, NB>(), NW>()];
+  const float* ps = (const float*)lds;
+  prod_tile<RT, NB, NN, NW, S>(a, m0, n0, lds);
   for (int pi = tid; pi < TM * TN; pi += 64 * NW) {
     const int ml = pi / TN, nl = pi % TN;
     const int m = m0 + ml;
@@ -516,6 +537,65 @@ __global__ __launch_bounds__(64 * NW) void prod_wide(ProdArgs a) {
 // Forward: y_{l+1} = y_l + relu(z_l).  Adjoint (recomputation of layer l):
 // ybar_{l+1} = nn_in (= ybar_{l+2} + zbar_{l+1} W_{l+1}, from the product
 // launch before it) plus the loss seed; zbar_l = ybar_{l+1} 1[z_l > 0].
+// The epilogue over a 64 x 64 tile: zsum(ml, nl) is z_l without its bias
+// (or, CACHED, unused: z_l is a.zc_in), nn(ml, nl, o) is nn_in's element.
+template <int MODE, bool CACHED, int NW, class ZS, class NNI>
+__device__ __forceinline__ void mlp_epilogue(const MlpArgs& a, int tile, int m0, int n0, ZS zsum, NNI nn) {
+  constexpr int TM = 64, TN = 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, B = a.B, w = a.w;
+  float lterm = 0.f;
+  for (int pi = tid; pi < TM * TN; pi += 64 * NW) {
+#pragma clang fp contract(on)  // the same bits with and without the product
+    const int ml = pi / TN, nl = pi % TN;
+    const int m = m0 + ml, c = n0 + nl;
+    if (m >= B) continue;
+    const size_t o = (size_t)m * w + c;
+    const float z = CACHED ? a.zc_in[o] : zsum(ml, nl) + a.bias[c];
+    if (MODE == kForward && a.zc_out) a.zc_out[o] = z;
+    const float yv = (float)((const __bf16*)a.y)[o];
+    const __bf16 y1s = (__bf16)(yv + fmaxf(z, 0.f));
+    if (MODE == kForward) {
+      ((__bf16*)a.y_out)[o] = y1s;
+    } else {
+      const float hl = (float)y1s;  // the loss reads the stored y_{l+1}
+      float yb;
+      if (a.first) {
+        if (a.loss == AMBPTT_LOSS_HALF_SQ_LAST) {
+          yb = hl;
+          lterm += hl * hl;
+        } else if (a.loss == AMBPTT_LOSS_MEAN_LAST) {
+          yb = a.inv_bw;
+          lterm += hl;
+        } else {
+          yb = 2.f * hl * a.inv_bw;
+          lterm += hl * hl;
+        }
+      } else {
+        yb = nn(ml, nl, o);
+        if (a.loss == AMBPTT_LOSS_MEAN_SQ_ALL) {
+          yb += 2.f * hl * a.inv_bw;
+          lterm += hl * hl;
+        }
+      }
+      a.ybar_out[o] = yb;
+      ((__bf16*)a.zbar_out)[o] = (__bf16)(z > 0.f ? yb : 0.f);
+      ((__bf16*)a.ywin_out)[o] = ((const __bf16*)a.y)[o];
+    }
+  }
+  if (MODE == kAdjoint) {
+    const float s = wave_sum(lterm);
+    __shared__ float wsum[NW];
+    if (lane == 0) wsum[wave] = s;
+    __syncthreads();
+    if (tid == 0) {
+      float t = 0.f;
+#pragma unroll
+      for (int wv = 0; wv < NW; ++wv) t += wsum[wv];
+      a.loss_acc[tile] += (double)t;
+    }
+  }
+}
+
 template <int MODE, int NW = kWaves, int S = 2>
 __global__ __launch_bounds__(64 * NW) void mlp_wide(MlpArgs a) {
   constexpr int RT = 4, NB = 4, TM = 64, TN = 64;
@@ -549,55 +629,26 @@ __global__ __launch_bounds__(64 * NW) void mlp_wide(MlpArgs a) {
   }
   __syncthreads();
 
-  float lterm = 0.f;
-  for (int pi = tid; pi < TM * TN; pi += 64 * NW) {
-    const int ml = pi / TN, nl = pi % TN;
-    const int m = m0 + ml, c = n0 + nl;
-    if (m >= B) continue;
-    const size_t o = (size_t)m * w + c;
-    const float z = sum_partials<RT, NB, NW>(ps, ml, nl) + a.bias[c];
-    const float yv = (float)((const __bf16*)a.y)[o];
-    const __bf16 y1s = (__bf16)(yv + fmaxf(z, 0.f));
-    if (MODE == kForward) {
-      ((__bf16*)a.y_out)[o] = y1s;
-    } else {
-      const float hl = (float)y1s;  // the loss reads the stored y_{l+1}
-      float yb;
-      if (a.first) {
-        if (a.loss == AMBPTT_LOSS_HALF_SQ_LAST) {
-          yb = hl;
-          lterm += hl * hl;
-        } else if (a.loss == AMBPTT_LOSS_MEAN_LAST) {
-          yb = a.inv_bw;
-          lterm += hl;
-        } else {
-          yb = 2.f * hl * a.inv_bw;
-          lterm += hl * hl;
-        }
-      } else {
-        yb = a.nn_in[o];
-        if (a.loss == AMBPTT_LOSS_MEAN_SQ_ALL) {
-          yb += 2.f * hl * a.inv_bw;
-          lterm += hl * hl;
-        }
-      }
-      a.ybar_out[o] = yb;
-      ((__bf16*)a.zbar_out)[o] = (__bf16)(z > 0.f ? yb : 0.f);
-      ((__bf16*)a.ywin_out)[o] = ((const __bf16*)a.y)[o];
-    }
-  }
-  if (MODE == kAdjoint) {
-    const float s = wave_sum(lterm);
-    __shared__ float wsum[NW];
-    if (lane == 0) wsum[wave] = s;
-    __syncthreads();
-    if (tid == 0) {
-      float t = 0.f;
-#pragma unroll
-      for (int wv = 0; wv < NW; ++wv) t += wsum[wv];
-      a.loss_acc[tile] += (double)t;
-    }
-  }
+  mlp_epilogue<MODE, false, NW>(
+      a, tile, m0, n0, [&](int ml, int nl) { return sum_partials<RT, NB, NW>(ps, ml, nl); },
+      [&](int, int, size_t o) { return a.nn_in[o]; });
+}
+
+// The adjoint of a layer whose z_l is kept: the product zbar_{l+1} W_{l+1}
+// (on the same 64 x 64 tiles) and the layer's own adjoint in one launch.
+template <int NW = kWaves>
+__global__ __launch_bounds__(64 * NW) void mlp_back_wide(MlpArgs a) {
+  const int mg = (a.B + 63) / 64, ntile = mg * (a.w / 64);
+  const int tile = tile_of(ntile);
+  if (tile >= ntile) return;
+  const int m0 = (tile % mg) * 64, n0 = (tile / mg) * 64;
+  __shared__ __attribute__((aligned(16))) char lds[lds_bytes<4, 4, prod_scr<4, true, 4>(), NW>()];
+  const float* ps = (const float*)lds;
+  const ProdArgs pa{a.zbar_in, a.Wn, nullptr, nullptr, a.B, a.w, a.w};
+  prod_tile<4, 4, true, NW, 2>(pa, m0, n0, lds);
+  mlp_epilogue<kAdjoint, true, NW>(
+      a, tile, m0, n0, [](int, int) { return 0.f; },
+      [&](int ml, int nl, size_t o) { return a.ybar_in[o] + sum_partials<4, 4, NW>(ps, ml, nl); });
 }
 
 unsigned grid_for(int ntile) { return unsigned(8 * ((ntile + 7) / 8)); }
@@ -644,9 +695,11 @@ hipError_t launch_cell_wide(int G, int mode, const StepArgs& a, hipStream_t s, h
   const dim3 grid(grid_for(cell_wide_tiles(G, a.B, a.H))), block(64 * kWaves);
   if (G == 4) {
     if (mode == kForward) hipExtLaunchKernelGGL((cell_wide<4, kForward>), grid, block, 0, s, e0, e1, 0, a);
+    else if (a.zc_in) hipExtLaunchKernelGGL((cell_wide<4, kAdjoint, true>), grid, block, 0, s, e0, e1, 0, a);
     else hipExtLaunchKernelGGL((cell_wide<4, kAdjoint>), grid, block, 0, s, e0, e1, 0, a);
   } else {
     if (mode == kForward) hipExtLaunchKernelGGL((cell_wide<1, kForward>), grid, block, 0, s, e0, e1, 0, a);
+    else if (a.zc_in) hipExtLaunchKernelGGL((cell_wide<1, kAdjoint, true>), grid, block, 0, s, e0, e1, 0, a);
     else hipExtLaunchKernelGGL((cell_wide<1, kAdjoint>), grid, block, 0, s, e0, e1, 0, a);
   }
   return hipGetLastError();
@@ -671,6 +724,13 @@ hipError_t launch_prod_nn(const ProdArgs& a, hipStream_t s, hipEvent_t e0, hipEv
   if (a.K % 64 != 0 || a.N % 64 != 0 || a.M < 1) return hipErrorInvalidValue;
   const dim3 grid(grid_for(((a.M + 63) / 64) * (a.N / 64))), block(64 * kWaves);
   hipExtLaunchKernelGGL((prod_wide<4, 4, true>), grid, block, 0, s, e0, e1, 0, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_mlp_back_wide(const MlpArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  if (!mlp_wide_fits(a.B, a.w) || a.first || !a.zc_in) return hipErrorInvalidValue;
+  const dim3 grid(grid_for(mlp_wide_tiles(a.B, a.w))), block(64 * kWaves);
+  hipExtLaunchKernelGGL((mlp_back_wide<>), grid, block, 0, s, e0, e1, 0, a);
   return hipGetLastError();
 }
 
