@@ -21,8 +21,8 @@
 // Bound: the matrix cores at the clock that the power limit leaves them (see
 // gemm_f32x3.hip).  The 4096-LSTM's window (16384 x 5120, 8192 rows, 8.2
 // TFLOP of bf16 products) takes 6.8 ms against 10.8-11.6 ms on fp32 MFMAs,
-// 1.21 PFLOP/s; 4096 x 1120 over 7200 rows 0.59 ms against 0.99; 4096 x 1280
-// over 1024 rows 82 us against 124; one fp32 residual MLP layer, 1040 x 1040
+// 1.21 PFLOP/s; 4096 x 1120 over 7200 rows 0.50 ms against 0.99; 4096 x 1280
+// over 1024 rows 77 us against 124; one fp32 residual MLP layer, 1040 x 1040
 // over 70 rows, 9.5 us against 14.0; 320 x 288 over 320 rows 21 us against 34.
 #include <hip/hip_runtime.h>
 
@@ -204,8 +204,12 @@ bool dw_f32x3_fits(const DwArgs& a) {
 hipError_t launch_dw_f32x3(const DwArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (!dw_f32x3_fits(a)) return hipErrorInvalidValue;
   const int N = a.D + a.H;
-  // as for the gate product: the large tile where it fills most of the CUs
-  if (((a.GH + 255) / 256) * ((N + 127) / 128) >= 192) {
+  // A 32-row stage of a 256 x 128 tile takes 2.05 us, of two 128 x 64 tiles
+  // sharing a CU 1.3 us: the fewer rounds times those (4096 x 1120: 144 tiles
+  // in one round 496 us, 576 in two 588 us over 7200 rows)
+  const auto rounds = [](int t, int slots) { return double((t + slots - 1) / slots); };
+  const int big = ((a.GH + 255) / 256) * ((N + 127) / 128), small = ((a.GH + 127) / 128) * ((N + 63) / 64);
+  if (2.05 * rounds(big, 256) <= 1.3 * rounds(small, 512)) {
     hipExtLaunchKernelGGL((dw_f32x3<256, 128, 4, 2>), dim3((a.GH + 255) / 256, (N + 127) / 128), dim3(512), 0, s, e0, e1,
                           0, a);
   } else {

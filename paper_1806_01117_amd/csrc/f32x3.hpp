@@ -72,7 +72,8 @@ __device__ __forceinline__ bool any_bad(const f4 (&acc)[MI][NI]) {
 // The stages st0 .. st1 - 1 of one wave's MI x NI blocks of 16 x 16.
 // gload(st, p) brings piece p (of NP) of stage st to registers, put(buf, p)
 // splits it and writes it to LDS buffer `buf` (buffer 1: -A).  The stages go
-// in pairs: of a stage at or past st1, gload must give zeros for one operand.
+// in pairs (st1 - st0 is rounded up): of a stage past the last that counts,
+// gload must give zeros for one operand.
 // ard, brd: the lane's first fragments in a buffer of STAGE bytes; BLK: bytes
 // from one 16-row block to the next, its planes kFrag apart.
 //

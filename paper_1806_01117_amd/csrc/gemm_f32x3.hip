@@ -58,27 +58,33 @@ __device__ __forceinline__ void tile_of(int i, int mt, int nt, int* tm, int* tn)
   }
 }
 
-// One workgroup's product on a TM x TN tile: 4 or 8 waves of (TM / WM) x
-// (TN / WN).  A: rows of [x | h], fp32; B: planes in fragment order.
-template <int TM, int TN, int WM, int WN>
+// One workgroup's product on a TM x TN tile: KG groups of WM x WN waves, each
+// wave (TM / WM) x (TN / WN).  A: rows of [x | h], fp32; B: planes in fragment
+// order.  A group takes its own part of the stages, in LDS buffers of its own
+// (two groups give a SIMD two waves where the grid has fewer tiles than the
+// chip has CUs); the groups' sums meet in the epilogue.
+template <int TM, int TN, int WM, int WN, int KG>
 struct Tile {
-  static constexpr int NW = WM * WN, NT = 64 * NW;
+  static constexpr int NW = WM * WN, NT = 64 * NW;  // of one group
   static constexpr int MI = TM / WM / 16, NI = TN / WN / 16;
   static constexpr int PA = TM * 8 / NT;            // float4 of A per thread and stage
   static constexpr int PB = TN / 16 * 3 / NW;       // 16-byte pieces of B per thread and stage
   static constexpr int ABYTES = TM / 16 * kBlk, BBYTES = TN / 16 * kBlk;
   static constexpr int STAGE = ABYTES + BBYTES;
+  static constexpr int LDS = KG * 2 * STAGE;
   static_assert(TM * 8 % NT == 0 && TN / 16 * 3 % NW == 0 && MI % 2 == 0, "whole loads per thread, row blocks in pairs");
 
   // A's rows are [x | h], x: [M][D], h: [M][H], each padded to whole stages
   // (TWO false: h alone).  bblk(b) is the packed block row of the tile's
   // 16-column block b; kb its 32-wide steps.  What a padded stage reads of A
-  // past the end of a row meets zeros of B.
+  // past the end of a row meets zeros of B.  Stages st0 .. st1 - 1; len: the
+  // most stages that any group of the workgroup has (their barriers are
+  // common).  lds: the group's buffers.
   template <bool TWO, bool SCALE, class BBlk>
   static __device__ __forceinline__ void run(const float* x, const float* h, int M, int D, int H, int m0,
-                                             const char* Bp, unsigned bbytes, int kb, int st0, int st1, BBlk bblk,
-                                             char* lds, f4 (&acc)[MI][NI]) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+                                             const char* Bp, unsigned bbytes, int kb, int st0, int st1, int len,
+                                             BBlk bblk, char* lds, f4 (&acc)[MI][NI]) {
+    const int tid = threadIdx.x % NT, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const int r = lane & 15, q = lane >> 4;
     const int kx = TWO ? (D + kSt - 1) / kSt : 0;  // x's stages
@@ -147,7 +153,7 @@ struct Tile {
     };
     const int ard = (wm * MI) * kBlk + (16 * q + (r ^ swz(q))) * 16;
     const int brd = ABYTES + (wn * NI) * kBlk + lane * 16;
-    x3_pipeline<MI, NI, PA + 1, STAGE, kBlk>(lds, ard, brd, st0, st1, gload, put, acc);
+    x3_pipeline<MI, NI, PA + 1, STAGE, kBlk>(lds, ard, brd, st0, st0 + len, gload, put, acc);
     if (SCALE) {
 #pragma unroll
       for (int i = 0; i < MI; ++i)
@@ -156,34 +162,36 @@ struct Tile {
     }
   }
 
-  // The wave's block by fp32 MFMAs from global memory; bval(j, k) is B of the
+  // The same sums by fp32 MFMAs from global memory; bval(j, k) is B of the
   // lane's column (l & 15) of the wave's column block j at reduction indices
-  // k .. k + 3.  K and D are multiples of 16.
+  // k .. k + 3 of [x | h].  D and H are multiples of 16.
   template <class BVal>
-  static __device__ __forceinline__ void exact(const float* x, const float* h, int M, int D, int H, int m0, int k0,
-                                               int k1, BVal bval, f4 (&acc)[MI][NI]) {
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave / WN;
+  static __device__ __forceinline__ void exact(const float* x, const float* h, int M, int D, int H, int m0, int st0,
+                                               int st1, BVal bval, f4 (&acc)[MI][NI]) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) % NW;
+    const int wm = wave / WN, kx = stages(D);
     const int r = lane & 15, q = lane >> 4;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NI; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-    for (int k = k0; k < k1; k += 16) {
-      f4 av[MI], bv[NI];
-      const bool inx = k < D;
+    for (int c = 2 * st0; c < 2 * st1; ++c) {  // 16 reduction indices each
+      const bool inx = c < 2 * kx;
       const float* base = inx ? x : h;
-      const int ld = inx ? D : H, kk = (inx ? k : k - D) + 4 * q;
+      const int ld = inx ? D : H, kk = 16 * (inx ? c : c - 2 * kx);
+      if (kk >= ld) continue;  // the padding of a segment
+      f4 av[MI], bv[NI];
 #pragma unroll
-      for (int i = 0; i < MI; ++i) av[i] = *(const f4*)(base + (size_t)min(m0 + (wm * MI + i) * 16 + r, M - 1) * ld + kk);
+      for (int i = 0; i < MI; ++i)
+        av[i] = *(const f4*)(base + (size_t)min(m0 + (wm * MI + i) * 16 + r, M - 1) * ld + kk + 4 * q);
 #pragma unroll
-      for (int j = 0; j < NI; ++j) bv[j] = bval(j, k + 4 * q);
+      for (int j = 0; j < NI; ++j) bv[j] = bval(j, (inx ? kk : D + kk) + 4 * q);
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
+      for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int j = 0; j < NI; ++j) acc[i][j] = mfma_f32_16x16x4(av[i][c], bv[j][c], acc[i][j]);
+          for (int j = 0; j < NI; ++j) acc[i][j] = mfma_f32_16x16x4(av[i][e], bv[j][e], acc[i][j]);
     }
   }
 };
@@ -307,14 +315,15 @@ __device__ __forceinline__ void add_loss(const StepArgs& a, float lterm, float* 
 // Tile: TM batch rows x TN gate columns = U = TN / G units of all G gates
 // (16-column block b of the tile: gate b / (U / 16)).  The finished tile goes
 // to the epilogue through LDS.
-template <int G, int MODE, int TM, int TN, int WM, int WN>
-__global__ __launch_bounds__(64 * WM * WN) void cell_f32x3(StepArgs a) {
-  using T = Tile<TM, TN, WM, WN>;
+template <int G, int MODE, int TM, int TN, int WM, int WN, int KG>
+__global__ __launch_bounds__(64 * WM * WN * KG) void cell_f32x3(StepArgs a) {
+  using T = Tile<TM, TN, WM, WN, KG>;
   constexpr int U = TN / G, UB = U / 16, LZ = TN + 4;
-  constexpr int LDS = 2 * T::STAGE > TM * LZ * 4 ? 2 * T::STAGE : TM * LZ * 4;
+  constexpr int LDS = T::LDS > KG * TM * LZ * 4 ? T::LDS : KG * TM * LZ * 4;
   __shared__ __attribute__((aligned(16))) char lds[LDS];
-  __shared__ float red[T::NW];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __shared__ float red[T::NW * KG];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kg = wv / T::NW, wave = wv % T::NW;
   const int wm = wave / WN, wn = wave % WN;
   const int r = lane & 15, q = lane >> 4;
   const int B = a.B, D = a.D, H = a.H, K1 = D + H, GH = G * H;
@@ -332,55 +341,64 @@ __global__ __launch_bounds__(64 * WM * WN) void cell_f32x3(StepArgs a) {
 #pragma unroll
     for (int j = 0; j < T::NI; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
   const int kb = stages(D) + stages(H);
+  const int st0 = kg * kb / KG, st1 = (kg + 1) * kb / KG, len = (kb + KG - 1) / KG;
   T::template run<true, false>((const float*)a.x, (const float*)a.h, B, D, H, m0, (const char*)a.Wx3,
-                               unsigned(GH / 16) * unsigned(kb) * unsigned(kBlk), kb, 0, kb, bblk, lds, acc);
+                               unsigned(GH / 16) * unsigned(kb) * unsigned(kBlk), kb, st0, st1, len, bblk,
+                               lds + kg * 2 * T::STAGE, acc);
+  if (KG > 1) __syncthreads();  // every group has left its buffers
   if (any_bad(acc)) {
     const float* W = (const float*)a.W;
-    T::exact((const float*)a.x, (const float*)a.h, B, D, H, m0, 0, K1,
+    T::exact((const float*)a.x, (const float*)a.h, B, D, H, m0, st0, st1,
              [&](int j, int k) {
                return *(const f4*)(W + (size_t)(16 * bblk(wn * T::NI + j) + r) * K1 + k);
              },
              acc);
   }
-  float* z = (float*)lds;
+  float* z = (float*)lds;  // one tile per group
 #pragma unroll
   for (int i = 0; i < T::MI; ++i)
 #pragma unroll
     for (int j = 0; j < T::NI; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        z[((wm * T::MI + i) * 16 + 4 * q + v) * LZ + (wn * T::NI + j) * 16 + r] = acc[i][j][v];
+        z[kg * TM * LZ + ((wm * T::MI + i) * 16 + 4 * q + v) * LZ + (wn * T::NI + j) * 16 + r] = acc[i][j][v];
   __syncthreads();
 
-  const float lterm = cell_epilogue<G, MODE, TM, U, T::NT>(a, m0, j0, [&](int g, int row, int j) {
-    return *(const f4*)(z + row * LZ + g * U + (j - j0)) + *(const f4*)(a.bias + g * H + j);
+  const float lterm = cell_epilogue<G, MODE, TM, U, T::NT * KG>(a, m0, j0, [&](int g, int row, int j) {
+    const float* zr = z + row * LZ + g * U + (j - j0);
+    f4 v = *(const f4*)zr;
+#pragma unroll
+    for (int k = 1; k < KG; ++k) v += *(const f4*)(zr + k * TM * LZ);
+    return v + *(const f4*)(a.bias + g * H + j);
   });
-  if (MODE == kAdjoint) add_loss<T::NW>(a, lterm, red);
+  if (MODE == kAdjoint) add_loss<T::NW * KG>(a, lterm, red);
 }
 
 // The adjoint of a step whose pre-activations are kept: the same tiles and
 // the same threads for the same elements (so the same loss sums), without the
 // product.  Bound by HBM: 5 [B][4 H] or so arrays of the LSTM in and out.
-template <int G, int TM, int TN, int WM, int WN>
-__global__ __launch_bounds__(64 * WM * WN) void cell_back_f32x3(StepArgs a) {
+template <int G, int TM, int TN, int NW>
+__global__ __launch_bounds__(64 * NW) void cell_back_f32x3(StepArgs a) {
   constexpr int U = TN / G;
-  __shared__ float red[WM * WN];
+  __shared__ float red[NW];
   int tm, tn;
   tile_of(blockIdx.x, (a.B + TM - 1) / TM, (a.H + U - 1) / U, &tm, &tn);
-  const float lterm = cell_epilogue<G, kAdjoint, TM, U, 64 * WM * WN>(a, tm * TM, tn * U, [&](int g, int row, int j) {
+  const float lterm = cell_epilogue<G, kAdjoint, TM, U, 64 * NW>(a, tm * TM, tn * U, [&](int g, int row, int j) {
     return *(const f4*)(a.zc_in + (size_t)(tm * TM + row) * (G * a.H) + g * a.H + j);
   });
-  add_loss<WM * WN>(a, lterm, red);
+  add_loss<NW>(a, lterm, red);
 }
 
 // ---- h-adjoint product: out = zbar W_h, the reduction split --------------------
 // Part s of `parts` contiguous runs of stages goes to out + s M N; the
 // adjoint (or sum_parts) adds the parts in order.
-template <int TM, int TN, int WM, int WN>
-__global__ __launch_bounds__(64 * WM * WN) void prod_f32x3(ProdArgs a, int parts) {
-  using T = Tile<TM, TN, WM, WN>;
-  __shared__ __attribute__((aligned(16))) char lds[2 * T::STAGE];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+template <int TM, int TN, int WM, int WN, int KG>
+__global__ __launch_bounds__(64 * WM * WN * KG) void prod_f32x3(ProdArgs a, int parts) {
+  using T = Tile<TM, TN, WM, WN, KG>;
+  __shared__ __attribute__((aligned(16))) char lds[T::LDS];
+  static_assert(T::LDS >= (KG - 1) * T::NT * T::MI * T::NI * 16, "the groups' sums fit the stages' LDS");
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kg = wv / T::NW, wave = wv % T::NW;
   const int wm = wave / WN, wn = wave % WN;
   const int r = lane & 15, q = lane >> 4;
   const int M = a.M, N = a.N, K = a.K;
@@ -390,7 +408,8 @@ __global__ __launch_bounds__(64 * WM * WN) void prod_f32x3(ProdArgs a, int parts
   const int tn = tc / parts, part = tc % parts;
   const int m0 = tm * TM, n0 = tn * TN;
   const int kb = stages(K);
-  const int st0 = int((long)part * kb / parts), st1 = int((long)(part + 1) * kb / parts);
+  const int np = parts * KG, pt = part * KG + kg;
+  const int st0 = int((long)pt * kb / np), st1 = int((long)(pt + 1) * kb / np), len = (kb + np - 1) / np;
   auto bblk = [&](int b) { return min(n0 / 16 + b, N / 16 - 1); };  // columns past N: the last 16 again, unused
   f4 acc[T::MI][T::NI];
 #pragma unroll
@@ -398,15 +417,34 @@ __global__ __launch_bounds__(64 * WM * WN) void prod_f32x3(ProdArgs a, int parts
 #pragma unroll
     for (int j = 0; j < T::NI; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
   T::template run<false, true>((const float*)a.A, (const float*)a.A, M, 0, K, m0, (const char*)a.B,
-                               unsigned(N / 16) * unsigned(kb) * unsigned(kBlk), kb, st0, st1, bblk, lds, acc);
+                               unsigned(N / 16) * unsigned(kb) * unsigned(kBlk), kb, st0, st1, len, bblk,
+                               lds + kg * 2 * T::STAGE, acc);
   if (any_bad(acc)) {
     const float* W = a.Bf;  // B(k, n) = W[k ldb + n]
-    T::exact((const float*)a.A, (const float*)a.A, M, 0, K, m0, st0 * kSt, min(st1 * kSt, K),
+    T::exact((const float*)a.A, (const float*)a.A, M, 0, K, m0, st0, st1,
              [&](int j, int k) {
                const float* s = W + (size_t)k * a.ldb + 16 * bblk(wn * T::NI + j) + r;
                return f4{s[0], s[a.ldb], s[2 * (size_t)a.ldb], s[3 * (size_t)a.ldb]};
              },
              acc);
+  }
+  if (KG > 1) {  // the other groups' sums, in order, through LDS
+    f4* g = (f4*)lds;
+    const int t = threadIdx.x % T::NT;
+    __syncthreads();
+    if (kg > 0)
+#pragma unroll
+      for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+        for (int j = 0; j < T::NI; ++j) g[(((kg - 1) * T::MI + i) * T::NI + j) * T::NT + t] = acc[i][j];
+    __syncthreads();
+    if (kg > 0) return;
+#pragma unroll
+    for (int k = 0; k < KG - 1; ++k)
+#pragma unroll
+      for (int i = 0; i < T::MI; ++i)
+#pragma unroll
+        for (int j = 0; j < T::NI; ++j) acc[i][j] += g[((k * T::MI + i) * T::NI + j) * T::NT + t];
   }
   float* out = a.out + (size_t)part * M * N;
 #pragma unroll
@@ -489,28 +527,55 @@ bool f32x3_fits(int G, int B, int D, int H) {
 }
 
 namespace {
+
+// The two tiles: 256 x 128 on 8 waves moves the fewest operand bytes per MFMA;
+// 128 x 64 on two groups of 4 waves makes more workgroups of a small grid.
+// One workgroup of either fills a CU.  A 32-wide stage of the first takes
+// 2.05 us (300 x 9856 x 2672, 84 stages, 154 tiles: 167 us; 2.55 us with all
+// CUs at it, whose clock then falls), of the second 0.75 us (the same in two
+// rounds of 462 tiles: 126 us; 300 x 4096 x 1120: 31.5 us, with one group of 4
+// waves 39.5 us), so the second is taken where its rounds over the 256 CUs are
+// fewer than 2.7 times the first's (300 x 12288 x 3136, 3 rounds against 1:
+// 214 us against 202).
+constexpr double kBigStage = 2.05, kSmallStage = 0.75;
+double rounds(int tiles) { return double((tiles + 255) / 256); }
+bool big_tiles(int big, int small) { return rounds(big) * kBigStage <= rounds(small) * kSmallStage; }
+
 template <int G, int MODE>
 hipError_t cell_launch(const StepArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   const auto tiles = [&](int tm, int tn) { return ((a.B + tm - 1) / tm) * ((a.H + tn / G - 1) / (tn / G)); };
-  // 256 x 128 tiles move the fewest operand bytes per MFMA and fill a CU with
-  // one workgroup, so they need most of the 256 CUs; fewer tiles go 128 x 64,
-  // two workgroups to a CU (300 x 4096 x 1120: 64 tiles of 256 x 128, 192 of
-  // 128 x 64)
-  if (tiles(256, 128) >= 192) {
-    if (MODE == kAdjoint && a.zc_in)
-      hipExtLaunchKernelGGL((cell_back_f32x3<G, 256, 128, 4, 2>), dim3(tiles(256, 128)), dim3(512), 0, s, e0, e1, 0, a);
-    else
-      hipExtLaunchKernelGGL((cell_f32x3<G, MODE, 256, 128, 4, 2>), dim3(tiles(256, 128)), dim3(512), 0, s, e0, e1, 0, a);
-  } else if (MODE == kAdjoint && a.zc_in) {
-    hipExtLaunchKernelGGL((cell_back_f32x3<G, 128, 64, 4, 1>), dim3(tiles(128, 64)), dim3(256), 0, s, e0, e1, 0, a);
+  const int big = tiles(256, 128), small = tiles(128, 64);
+  const bool back = MODE == kAdjoint && a.zc_in;
+  if (big_tiles(big, small)) {
+    if (back) hipExtLaunchKernelGGL((cell_back_f32x3<G, 256, 128, 8>), dim3(big), dim3(512), 0, s, e0, e1, 0, a);
+    else hipExtLaunchKernelGGL((cell_f32x3<G, MODE, 256, 128, 4, 2, 1>), dim3(big), dim3(512), 0, s, e0, e1, 0, a);
   } else {
-    hipExtLaunchKernelGGL((cell_f32x3<G, MODE, 128, 64, 4, 1>), dim3(tiles(128, 64)), dim3(256), 0, s, e0, e1, 0, a);
+    if (back) hipExtLaunchKernelGGL((cell_back_f32x3<G, 128, 64, 8>), dim3(small), dim3(512), 0, s, e0, e1, 0, a);
+    else hipExtLaunchKernelGGL((cell_f32x3<G, MODE, 128, 64, 4, 1, 2>), dim3(small), dim3(512), 0, s, e0, e1, 0, a);
   }
   return hipGetLastError();
 }
+
+// the h-adjoint product's tile and split: the least of rounds x stages
+struct ProdPlan {
+  bool big;
+  int parts, tiles;
+};
+ProdPlan prod_plan(int M, int N, int K) {
+  const int kb = stages(K);
+  const int t[2] = {((M + 127) / 128) * ((N + 63) / 64), ((M + 255) / 256) * ((N + 127) / 128)};
+  ProdPlan best{false, 1, t[0]};
+  double least = 1e30;
+  for (int big = 0; big < 2; ++big)
+    for (int parts = 1; parts <= kProdSplitMax && parts * 16 <= kb; parts *= 2) {
+      const double c = rounds(t[big] * parts) * ((kb + parts - 1) / parts) * (big ? kBigStage : kSmallStage);
+      if (c < 0.97 * least) least = c, best = ProdPlan{big == 1, parts, t[big]};  // more parts must pay for their sum
+    }
+  return best;
+}
 }  // namespace
 
-int cell_f32x3_tiles(int G, int B, int H) {  // the most workgroups that any of its launches has
+int cell_f32x3_tiles(int G, int B, int H) {  // the most workgroups that its launches have
   return ((B + 127) / 128) * ((H + 64 / G - 1) / (64 / G));
 }
 
@@ -521,24 +586,14 @@ hipError_t launch_cell_f32x3(int G, int mode, const StepArgs& a, hipStream_t s, 
   return mode == kForward ? cell_launch<1, kForward>(a, s, e0, e1) : cell_launch<1, kAdjoint>(a, s, e0, e1);
 }
 
-int prod_f32x3_parts(int M, int N, int K) {
-  const int tiles = ((M + 255) / 256) * ((N + 127) / 128);
-  int parts = 1;
-  while (parts < kProdSplitMax && tiles * parts * 2 <= 256 && (K / kSt) / (2 * parts) >= 16) parts *= 2;
-  return parts;
-}
+int prod_f32x3_parts(int M, int N, int K) { return prod_plan(M, N, K).parts; }
 
-hipError_t launch_prod_f32x3(const ProdArgs& a, int parts, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  if (a.M < 1 || a.N < 16 || a.N % 16 || a.K < 16 || a.K % 16 || a.add || !a.Bf || parts < 1 || parts > kProdSplitMax ||
-      parts > (a.K + kSt - 1) / kSt)
-    return hipErrorInvalidValue;
-  const int tiles = ((a.M + 255) / 256) * ((a.N + 127) / 128);
-  if (tiles * parts >= 192) {
-    hipExtLaunchKernelGGL((prod_f32x3<256, 128, 4, 2>), dim3(tiles * parts), dim3(512), 0, s, e0, e1, 0, a, parts);
-  } else {
-    const int small = ((a.M + 127) / 128) * ((a.N + 63) / 64);
-    hipExtLaunchKernelGGL((prod_f32x3<128, 64, 4, 1>), dim3(small * parts), dim3(256), 0, s, e0, e1, 0, a, parts);
-  }
+hipError_t launch_prod_f32x3(const ProdArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  if (a.M < 1 || a.N < 16 || a.N % 16 || a.K < 16 || a.K % 16 || a.add || !a.Bf) return hipErrorInvalidValue;
+  const ProdPlan p = prod_plan(a.M, a.N, a.K);
+  const dim3 grid(p.tiles * p.parts), block(512);
+  if (p.big) hipExtLaunchKernelGGL((prod_f32x3<256, 128, 4, 2, 1>), grid, block, 0, s, e0, e1, 0, a, p.parts);
+  else hipExtLaunchKernelGGL((prod_f32x3<128, 64, 4, 1, 2>), grid, block, 0, s, e0, e1, 0, a, p.parts);
   return hipGetLastError();
 }
 

@@ -213,9 +213,9 @@ hipError_t launch_pack_f32x3(const float* src, int N, int K0, int K1, int ld, bo
 int cell_f32x3_tiles(int G, int B, int H);
 hipError_t launch_cell_f32x3(int G, int mode, const StepArgs& a, hipStream_t s, hipEvent_t e0 = nullptr,
                              hipEvent_t e1 = nullptr);
+// zbar W_h in prod_f32x3_parts partial sums: part s to out + s M N
 int prod_f32x3_parts(int M, int N, int K);
-hipError_t launch_prod_f32x3(const ProdArgs& a, int parts, hipStream_t s, hipEvent_t e0 = nullptr,
-                             hipEvent_t e1 = nullptr);
+hipError_t launch_prod_f32x3(const ProdArgs& a, hipStream_t s, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 // out = the sum, in order, of `parts` arrays of n floats
 hipError_t launch_sum_parts_f32(const float* p, int parts, size_t n, float* out, hipStream_t s,
                                 hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);

@@ -961,7 +961,7 @@ struct Exec {
         ProdArgs pa{a.zbar_in, wide ? WhPk : WhT, nullptr, hbuf, p.batch, p.hidden, L.G * p.hidden, L.ld_wht};
         if (x3) pa = x3_prod(a.zbar_in, hbuf);
         s = timed(AMBPTT_K_HADJ, [&](hipEvent_t e0, hipEvent_t e1) {
-          if (x3) return launch_prod_f32x3(pa, hparts, C->cs, e0, e1);
+          if (x3) return launch_prod_f32x3(pa, C->cs, e0, e1);
           if (hparts > 1) return launch_prod_split_f32(pa, hparts, C->cs, e0, e1);
           return wide ? launch_prod_nt(pa, C->cs, e0, e1) : prod32(pa, e0, e1);
         });
@@ -1067,7 +1067,7 @@ struct Exec {
     a.dc0 = dc0;
     if (x3) {  // dL/dh_0 = zbar_0 W_h in parts, then their sum
       ambptt_status s = timed(AMBPTT_K_OTHER, [&](hipEvent_t e0, hipEvent_t e1) {
-        return launch_prod_f32x3(x3_prod(a.zbar_in, hbuf), hparts, C->cs, e0, e1);
+        return launch_prod_f32x3(x3_prod(a.zbar_in, hbuf), C->cs, e0, e1);
       });
       if (s != AMBPTT_OK) return s;
       HIPCK(launch_sum_parts_f32(hbuf, hparts, (size_t)p.batch * p.hidden, dh0, C->cs));
