@@ -231,7 +231,11 @@ __global__ void transpose_wh_u16(const uint16_t* __restrict__ W, uint16_t* __res
 hipError_t launch_dw_bf16(const DwArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (a.GH % 8 != 0 || a.D % 8 != 0 || a.H % 8 != 0 || a.R < 1) return hipErrorInvalidValue;
   const int N = a.D + a.H;
-  if (a.R <= 512) {  // a few stages: the fp32 tile's write outweighs forming it
+  // A few stages: the fp32 tile's write outweighs forming it.  Few 256 x 192
+  // tiles: 128 x 128 put more CUs to work (1536 x 1600 over 4000 rows: 54 tiles
+  // 141 us, 156 tiles 115 us; 4096 x 1536 over 8200: 128 tiles 264 us, 384
+  // tiles 233 us; the 2048-LSTM's window: 512 tiles 500 us, 1536 tiles 570 us).
+  if (a.R <= 512 || ((a.GH + 255) / 256) * ((N + 191) / 192) < 192) {
     dim3 grid((a.GH + 127) / 128, (N + 127) / 128);
     hipExtLaunchKernelGGL((dw_bf16<128, 128>), grid, dim3(256), 0, s, e0, e1, 0, a);
   } else {

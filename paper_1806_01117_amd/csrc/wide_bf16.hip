@@ -8,6 +8,8 @@
 //   * Tiles move the fewest bytes per CU: a 64 x 64 output tile per
 //     workgroup for the cell's gate GEMM (64 batch rows x 16 LSTM units, all
 //     four gates) and for the MLP layer, 32 x 32 for the h-adjoint product.
+//     Problems that would leave most of the 256 CUs without a tile take 32 or
+//     16 rows per tile instead (tile_rows).
 //     The adjoint's products hbar = zbar W_h (cell) and zbar W_{l+1} (MLP)
 //     are launches of their own: each reads the whole zbar of its rows, and
 //     fused into the cell kernel's tile they would move twice the bytes.
@@ -269,7 +271,7 @@ constexpr int lds_bytes() {
 
 // ---- the recurrent cell: gate GEMM + cell update ----------------------------
 //
-// Workgroup tile: 64 batch rows x UN hidden units, all G gates (64 gate
+// Workgroup tile: 16 RT batch rows x UN hidden units, all G gates (64 gate
 // columns: UN = 16 for the LSTM, 64 for the tanh RNN).  Gate column n =
 // g UN + u is weight row g H + j0 + u; a 16-column group is 16 consecutive
 // weight rows, one n tile of the fragment-order copy of W (a.W: pack_nt of
@@ -280,9 +282,9 @@ constexpr int lds_bytes() {
 // CACHED (adjoint): the pre-activations are kept (a.zc_in) and the gate
 // product is not formed again; the same tiles and threads take the same
 // elements.
-template <int G, int MODE, bool CACHED = false, int NW = kWaves, int S = 2>
+template <int G, int MODE, int RT, bool CACHED = false, int NW = kWaves, int S = RT == 4 ? 2 : 3>
 __global__ __launch_bounds__(64 * NW) void cell_wide(StepArgs a) {
-  constexpr int RT = 4, NB = 4, TM = 64;
+  constexpr int NB = 4, TM = 16 * RT;
   constexpr int UN = 64 / G;  // hidden units of the tile
   constexpr int SCR = (RT + NB) * kSlot;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -537,11 +539,11 @@ __global__ __launch_bounds__(64 * NW) void prod_wide(ProdArgs a) {
 // Forward: y_{l+1} = y_l + relu(z_l).  Adjoint (recomputation of layer l):
 // ybar_{l+1} = nn_in (= ybar_{l+2} + zbar_{l+1} W_{l+1}, from the product
 // launch before it) plus the loss seed; zbar_l = ybar_{l+1} 1[z_l > 0].
-// The epilogue over a 64 x 64 tile: zsum(ml, nl) is z_l without its bias
+// The epilogue over a 16 RT x 64 tile: zsum(ml, nl) is z_l without its bias
 // (or, CACHED, unused: z_l is a.zc_in), nn(ml, nl, o) is nn_in's element.
-template <int MODE, bool CACHED, int NW, class ZS, class NNI>
+template <int MODE, int RT, bool CACHED, int NW, class ZS, class NNI>
 __device__ __forceinline__ void mlp_epilogue(const MlpArgs& a, int tile, int m0, int n0, ZS zsum, NNI nn) {
-  constexpr int TM = 64, TN = 64;
+  constexpr int TM = 16 * RT, TN = 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, B = a.B, w = a.w;
   float lterm = 0.f;
   for (int pi = tid; pi < TM * TN; pi += 64 * NW) {
@@ -596,9 +598,9 @@ __device__ __forceinline__ void mlp_epilogue(const MlpArgs& a, int tile, int m0,
   }
 }
 
-template <int MODE, int NW = kWaves, int S = 2>
+template <int MODE, int RT, int NW = kWaves, int S = RT == 4 ? 2 : 3>
 __global__ __launch_bounds__(64 * NW) void mlp_wide(MlpArgs a) {
-  constexpr int RT = 4, NB = 4, TM = 64, TN = 64;
+  constexpr int NB = 4, TM = 16 * RT, TN = 64;
   constexpr int SCR = (RT + NB) * kSlot;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int B = a.B, w = a.w;
@@ -629,27 +631,43 @@ __global__ __launch_bounds__(64 * NW) void mlp_wide(MlpArgs a) {
   }
   __syncthreads();
 
-  mlp_epilogue<MODE, false, NW>(
+  mlp_epilogue<MODE, RT, false, NW>(
       a, tile, m0, n0, [&](int ml, int nl) { return sum_partials<RT, NB, NW>(ps, ml, nl); },
       [&](int, int, size_t o) { return a.nn_in[o]; });
 }
 
 // The adjoint of a layer whose z_l is kept: the product zbar_{l+1} W_{l+1}
-// (on the same 64 x 64 tiles) and the layer's own adjoint in one launch.
-template <int NW = kWaves>
+// (on the same tiles) and the layer's own adjoint in one launch.
+template <int RT, int NW = kWaves>
 __global__ __launch_bounds__(64 * NW) void mlp_back_wide(MlpArgs a) {
-  const int mg = (a.B + 63) / 64, ntile = mg * (a.w / 64);
+  constexpr int TM = 16 * RT;
+  const int mg = (a.B + TM - 1) / TM, ntile = mg * (a.w / 64);
   const int tile = tile_of(ntile);
   if (tile >= ntile) return;
-  const int m0 = (tile % mg) * 64, n0 = (tile / mg) * 64;
-  __shared__ __attribute__((aligned(16))) char lds[lds_bytes<4, 4, prod_scr<4, true, 4>(), NW>()];
+  const int m0 = (tile % mg) * TM, n0 = (tile / mg) * 64;
+  __shared__ __attribute__((aligned(16))) char lds[lds_bytes<RT, 4, prod_scr<RT, true, 4>(), NW>()];
   const float* ps = (const float*)lds;
   const ProdArgs pa{a.zbar_in, a.Wn, nullptr, nullptr, a.B, a.w, a.w};
-  prod_tile<4, 4, true, NW, 2>(pa, m0, n0, lds);
-  mlp_epilogue<kAdjoint, true, NW>(
+  prod_tile<RT, 4, true, NW, 2>(pa, m0, n0, lds);
+  mlp_epilogue<kAdjoint, RT, true, NW>(
       a, tile, m0, n0, [](int, int) { return 0.f; },
-      [&](int ml, int nl, size_t o) { return a.ybar_in[o] + sum_partials<4, 4, NW>(ps, ml, nl); });
+      [&](int ml, int nl, size_t o) { return a.ybar_in[o] + sum_partials<RT, 4, NW>(ps, ml, nl); });
 }
+
+// 16-row groups per tile for M rows and `cols` column tiles: 64 rows where
+// that makes 160 tiles or more, else 32, else 16.  Fewer rows read the weights
+// more often from L2 but put more CUs to work (forward step, 64 / 32 / 16
+// rows): 100 x 1536 x 1600 (tanh RNN) 12.7 / 9.6 / 7.2 us on 48 / 96 / 168
+// tiles; the LSTM at B = 128, D = 256, H = 1024 11.3 / 8.5 / 10.6 on 128 / 256
+// / 512; residual MLP layers 70 x 512 8.3 / 6.3 / 5.4, 128 x 2048 12.6 / 9.6 /
+// 8.2, 256 x 2048 12.9 / 10.6 / 13.7; the 2048-LSTM (256 tiles of 64 rows)
+// 16.0 / 20.3 / 25.9.
+int tile_rows(int M, int cols) {
+  for (int rt = 4; rt > 1; rt /= 2)
+    if (((M + 16 * rt - 1) / (16 * rt)) * cols >= 160) return rt;
+  return 1;
+}
+int row_tiles(int M, int cols) { return (M + 16 * tile_rows(M, cols) - 1) / (16 * tile_rows(M, cols)); }
 
 unsigned grid_for(int ntile) { return unsigned(8 * ((ntile + 7) / 8)); }
 
@@ -688,21 +706,29 @@ bool cell_wide_fits(int G, int B, int D, int H) {
 
 bool mlp_wide_fits(int B, int w) { return w % 64 == 0 && w > 0 && B > 0 && under_4g(size_t(w), size_t(w)) && under_4g(size_t(B), size_t(w)); }
 
-int cell_wide_tiles(int G, int B, int H) { return ((B + 63) / 64) * (H / (64 / G)); }
+int cell_wide_tiles(int G, int B, int H) { return row_tiles(B, H / (64 / G)) * (H / (64 / G)); }
+
+template <int G, int RT>
+static hipError_t launch_cell_wide_rt(int mode, const StepArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  const dim3 grid(grid_for(cell_wide_tiles(G, a.B, a.H))), block(64 * kWaves);
+  if (mode == kForward) hipExtLaunchKernelGGL((cell_wide<G, kForward, RT>), grid, block, 0, s, e0, e1, 0, a);
+  else if (a.zc_in) hipExtLaunchKernelGGL((cell_wide<G, kAdjoint, RT, true>), grid, block, 0, s, e0, e1, 0, a);
+  else hipExtLaunchKernelGGL((cell_wide<G, kAdjoint, RT>), grid, block, 0, s, e0, e1, 0, a);
+  return hipGetLastError();
+}
+
+template <int G>
+static hipError_t launch_cell_wide_g(int mode, const StepArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  switch (tile_rows(a.B, a.H / (64 / G))) {
+    case 4: return launch_cell_wide_rt<G, 4>(mode, a, s, e0, e1);
+    case 2: return launch_cell_wide_rt<G, 2>(mode, a, s, e0, e1);
+    default: return launch_cell_wide_rt<G, 1>(mode, a, s, e0, e1);
+  }
+}
 
 hipError_t launch_cell_wide(int G, int mode, const StepArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if ((mode != kForward && mode != kAdjoint) || !cell_wide_fits(G, a.B, a.D, a.H)) return hipErrorInvalidValue;
-  const dim3 grid(grid_for(cell_wide_tiles(G, a.B, a.H))), block(64 * kWaves);
-  if (G == 4) {
-    if (mode == kForward) hipExtLaunchKernelGGL((cell_wide<4, kForward>), grid, block, 0, s, e0, e1, 0, a);
-    else if (a.zc_in) hipExtLaunchKernelGGL((cell_wide<4, kAdjoint, true>), grid, block, 0, s, e0, e1, 0, a);
-    else hipExtLaunchKernelGGL((cell_wide<4, kAdjoint>), grid, block, 0, s, e0, e1, 0, a);
-  } else {
-    if (mode == kForward) hipExtLaunchKernelGGL((cell_wide<1, kForward>), grid, block, 0, s, e0, e1, 0, a);
-    else if (a.zc_in) hipExtLaunchKernelGGL((cell_wide<1, kAdjoint, true>), grid, block, 0, s, e0, e1, 0, a);
-    else hipExtLaunchKernelGGL((cell_wide<1, kAdjoint>), grid, block, 0, s, e0, e1, 0, a);
-  }
-  return hipGetLastError();
+  return G == 4 ? launch_cell_wide_g<4>(mode, a, s, e0, e1) : launch_cell_wide_g<1>(mode, a, s, e0, e1);
 }
 
 bool prod_wide_big(int M, int N) { return N % 32 == 0 && ((M + 31) / 32) * (N / 32) >= 192; }
@@ -720,29 +746,45 @@ hipError_t launch_prod_nt(const ProdArgs& a, hipStream_t s, hipEvent_t e0, hipEv
   return hipGetLastError();
 }
 
+int mlp_wide_tiles(int B, int w) { return row_tiles(B, w / 64) * (w / 64); }
+
 hipError_t launch_prod_nn(const ProdArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (a.K % 64 != 0 || a.N % 64 != 0 || a.M < 1) return hipErrorInvalidValue;
-  const dim3 grid(grid_for(((a.M + 63) / 64) * (a.N / 64))), block(64 * kWaves);
-  hipExtLaunchKernelGGL((prod_wide<4, 4, true>), grid, block, 0, s, e0, e1, 0, a);
+  const dim3 grid(grid_for(mlp_wide_tiles(a.M, a.N))), block(64 * kWaves);
+  switch (tile_rows(a.M, a.N / 64)) {
+    case 4: hipExtLaunchKernelGGL((prod_wide<4, 4, true>), grid, block, 0, s, e0, e1, 0, a); break;
+    case 2: hipExtLaunchKernelGGL((prod_wide<2, 4, true>), grid, block, 0, s, e0, e1, 0, a); break;
+    default: hipExtLaunchKernelGGL((prod_wide<1, 4, true>), grid, block, 0, s, e0, e1, 0, a); break;
+  }
   return hipGetLastError();
+}
+
+template <int RT>
+static hipError_t launch_mlp_wide_rt(int mode, const MlpArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  const dim3 grid(grid_for(mlp_wide_tiles(a.B, a.w))), block(64 * kWaves);
+  if (mode == kForward) hipExtLaunchKernelGGL((mlp_wide<kForward, RT>), grid, block, 0, s, e0, e1, 0, a);
+  else if (a.zc_in) hipExtLaunchKernelGGL((mlp_back_wide<RT>), grid, block, 0, s, e0, e1, 0, a);
+  else hipExtLaunchKernelGGL((mlp_wide<kAdjoint, RT>), grid, block, 0, s, e0, e1, 0, a);
+  return hipGetLastError();
+}
+
+static hipError_t launch_mlp_wide_any(int mode, const MlpArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  switch (tile_rows(a.B, a.w / 64)) {
+    case 4: return launch_mlp_wide_rt<4>(mode, a, s, e0, e1);
+    case 2: return launch_mlp_wide_rt<2>(mode, a, s, e0, e1);
+    default: return launch_mlp_wide_rt<1>(mode, a, s, e0, e1);
+  }
 }
 
 hipError_t launch_mlp_back_wide(const MlpArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (!mlp_wide_fits(a.B, a.w) || a.first || !a.zc_in) return hipErrorInvalidValue;
-  const dim3 grid(grid_for(mlp_wide_tiles(a.B, a.w))), block(64 * kWaves);
-  hipExtLaunchKernelGGL((mlp_back_wide<>), grid, block, 0, s, e0, e1, 0, a);
-  return hipGetLastError();
+  return launch_mlp_wide_any(kAdjoint, a, s, e0, e1);
 }
 
-int mlp_wide_tiles(int B, int w) { return ((B + 63) / 64) * (w / 64); }
-
 hipError_t launch_mlp_wide(int mode, const MlpArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  if (!mlp_wide_fits(a.B, a.w)) return hipErrorInvalidValue;
-  const dim3 grid(grid_for(mlp_wide_tiles(a.B, a.w))), block(64 * kWaves);
-  if (mode == kForward) hipExtLaunchKernelGGL((mlp_wide<kForward>), grid, block, 0, s, e0, e1, 0, a);
-  else if (mode == kAdjoint) hipExtLaunchKernelGGL((mlp_wide<kAdjoint>), grid, block, 0, s, e0, e1, 0, a);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  if ((mode != kForward && mode != kAdjoint) || !mlp_wide_fits(a.B, a.w) || (mode == kAdjoint && a.zc_in))
+    return hipErrorInvalidValue;
+  return launch_mlp_wide_any(mode, a, s, e0, e1);
 }
 
 }  // namespace ambptt
