@@ -149,7 +149,23 @@ int auto_window(const ambptt_problem* p) {
   return std::max(1, std::min(64, w));
 }
 
-Layout make_layout(const ambptt_problem* p, int window) {
+// Whether a bf16 problem of this size takes the wide kernels (where its shape
+// fits them): any batch of 48 rows, and smaller ones whose weights are many.
+// The wide path's adjoint is two launches, its kernels read the weights in
+// whole lines: at 20 x 1024 (D 512, 6.3 M weights) a forward step takes 6.9 us
+// against 8.1 and an adjoint 5.1 + 5.7 against 11-16, at 32 x 2048 (D 512)
+// 10.4 against 20.3 and 5.3 + 7.2 against 33.7; passes at 8 x 512 (D 128, 1.3 M)
+// are equal, at 32 x 1024 (tanh RNN, 1.2 M) 6 % slower.  The residual MLP's
+// kept adjoint is one launch on both: 20 x 1024 (1 M) 16 % faster, 40 x 4096
+// 33 %.
+bool wide_pays(const ambptt_problem* p) {
+  if (p->batch >= 48) return true;
+  const double H = p->hidden, weights = p->cell == AMBPTT_CELL_RESMLP ? 2.0 * H * H
+                                        : (p->cell == AMBPTT_CELL_LSTM ? 4.0 : 1.0) * H * (double(p->input) + H);
+  return weights >= double(1 << 21);
+}
+
+Layout make_layout(const ambptt_problem* p, int window, bool small_wide = true) {
   Layout L;
   L.G = p->cell == AMBPTT_CELL_LSTM ? 4 : 1;
   L.dsize = p->dtype == AMBPTT_BF16 ? 2 : 4;
@@ -179,7 +195,7 @@ Layout make_layout(const ambptt_problem* p, int window) {
     resmlp_grid(p->batch, p->hidden, &grid, &block);
     L.loss_slots = int(grid.x * grid.y);
   }
-  if (p->dtype == AMBPTT_BF16 && p->batch >= 48 &&
+  if (p->dtype == AMBPTT_BF16 && (small_wide || p->batch >= 48) && wide_pays(p) &&
       (L.mlp ? mlp_wide_fits(p->batch, p->hidden) : cell_wide_fits(L.G, p->batch, p->input, p->hidden))) {
     L.wide = true;
     const int tiles = L.mlp ? mlp_wide_tiles(p->batch, p->hidden) : cell_wide_tiles(L.G, p->batch, p->hidden);
@@ -223,8 +239,8 @@ Layout make_layout(const ambptt_problem* p, int window) {
   L.ld_wht = int(GH) + (pad_wht ? 32 : 0);
   L.off_wht = o; o += (L.mlp || L.mlpv) ? 0 : align_up((size_t)p->hidden * L.ld_wht * L.dsize);
   if (L.wide && !L.mlp) {
-    L.off_wpk = o; o += align_up(GH * size_t(p->input + p->hidden) * 2);
-    L.off_whpk = o; o += align_up(size_t(p->hidden) * GH * 2);
+    L.off_wpk = o; o += align_up(pack_nt_bytes(int(GH), p->input, p->hidden));
+    L.off_whpk = o; o += align_up(pack_nt_bytes(p->hidden, 0, int(GH)));
   }
   L.off_zbar = o; o += align_up(2 * (size_t)L.window * p->batch * GH * L.dsize);
   L.off_hwin = o; o += align_up(2 * (size_t)L.window * BH * L.dsize);
@@ -273,6 +289,12 @@ Layout make_layout(const ambptt_problem* p, int window) {
     o += size_t(L.zc_slots) * L.zc_bytes;
   }
   L.total = o;
+  // a small batch whose workspace fits the scratch array only without the
+  // wide kernels' copies of the weights keeps to the small kernels
+  if (L.wide && p->batch < 48 && L.total > kScratchBytes) {
+    const Layout S = make_layout(p, window, false);
+    if (S.total <= kScratchBytes) return S;
+  }
   return L;
 }
 
@@ -1306,8 +1328,8 @@ ambptt_status prepare_inputs(ambptt_ctx* C, const void* W, const void* h0, const
     HIPCK(launch_transpose_wh_bf16(W, E.WhT, L.G * p.hidden, p.input, p.hidden, C->cs));
     if (E.Wpk) {  // the wide kernels' fragment-order copies
       const int GH = L.G * p.hidden, K1 = p.input + p.hidden;
-      HIPCK(launch_pack_nt_bf16(W, GH, K1, K1, E.Wpk, C->cs));
-      HIPCK(launch_pack_nt_bf16(E.WhT, p.hidden, GH, L.ld_wht, E.WhPk, C->cs));
+      HIPCK(launch_pack_nt_bf16(W, GH, p.input, p.hidden, K1, E.Wpk, C->cs));
+      HIPCK(launch_pack_nt_bf16(E.WhT, p.hidden, 0, GH, L.ld_wht, E.WhPk, C->cs));
     }
   } else if (E.x3) {  // the split planes of W and of W_h^T
     const int GH = L.G * p.hidden, K1 = p.input + p.hidden;

@@ -80,47 +80,50 @@ __device__ __forceinline__ u4v bload(__amdgpu_buffer_rsrc_t r, unsigned voff, un
 // Rows of a row-major operand, read in 16-row groups and 64-wide reduction
 // blocks (128 bytes of a bf16 row).  Instruction h of group g covers rows
 // row0 + 16 g + 8 h + (lane >> 3), bytes 16 (lane & 7) .. +15 of the block.
+// A row of cols values that ends in the middle of a block (cols an odd
+// multiple of 32) reads zeros for the block's second half.
 struct Rows {
   __amdgpu_buffer_rsrc_t r;
   unsigned voff;    // lane part: (lane >> 3) stride + 16 (lane & 7)
+  unsigned vtail;   // ... in the block that the row ends in: past the buffer for its second half
   unsigned base;    // row0 stride (the same for the wave)
   unsigned stride;  // row stride in bytes
+  int half;         // the block that the row ends in the middle of (-1: none)
   __device__ __forceinline__ u4v load(int g, int h, int blk) const {
-    return bload(r, voff, base + unsigned(16 * g + 8 * h) * stride + unsigned(blk) * 128u);
-  }
-  // instruction h of the 16 rows starting at row `first` (an absolute row)
-  __device__ __forceinline__ u4v load_at(int first, int h, int blk) const {
-    return bload(r, voff, unsigned(first + 8 * h) * stride + unsigned(blk) * 128u);
+    return bload(r, blk == half ? vtail : voff, base + unsigned(16 * g + 8 * h) * stride + unsigned(blk) * 128u);
   }
 };
-__device__ __forceinline__ Rows rows_of(const void* p, unsigned bytes, int row0, int stride_bytes) {
+__device__ __forceinline__ Rows rows_of(const void* p, unsigned bytes, int row0, int cols) {
   const int lane = threadIdx.x & 63;
   Rows s;
   s.r = rsrc(p, bytes);
-  s.voff = unsigned((lane >> 3) * stride_bytes + 16 * (lane & 7));
-  s.base = unsigned(row0) * unsigned(stride_bytes);
-  s.stride = unsigned(stride_bytes);
+  s.voff = unsigned((lane >> 3) * (2 * cols) + 16 * (lane & 7));
+  s.vtail = (lane & 7) < 4 ? s.voff : bytes;
+  s.base = unsigned(row0) * unsigned(2 * cols);
+  s.stride = unsigned(2 * cols);
+  s.half = cols % 64 ? cols / 64 : -1;
   return s;
 }
+__host__ __device__ __forceinline__ int blocks(int cols) { return (cols + 63) / 64; }
 
 // An NT operand Bm(k, n) = B[n][k] in fragment order: the fragment of n tile
 // jt (columns 16 jt ..) and 32-wide reduction step ks is 1 KiB, lane l's 16
 // bytes being B[16 jt + (l & 15)][32 ks + 8 (l >> 4) .. +7], the operand
-// layout of v_mfma_f32_16x16x32_bf16; the K / 32 fragments of an n tile are
-// consecutive (n tile major).
+// layout of v_mfma_f32_16x16x32_bf16; the fragments of an n tile are
+// consecutive (n tile major), two per 64-wide block, padded with zeros.
 struct Frags {
   __amdgpu_buffer_rsrc_t r;
   unsigned voff;  // 16 lane
-  unsigned tile;  // bytes of one n tile: K / 32 fragments
+  unsigned tile;  // bytes of one n tile: its blocks' fragments
   __device__ __forceinline__ u4v load(int jt, int ks) const {
     return bload(r, voff, unsigned(jt) * tile + unsigned(ks) * 1024u);
   }
 };
-__device__ __forceinline__ Frags frags_of(const void* p, int N, int K) {
+__device__ __forceinline__ Frags frags_of(const void* p, int N, int nblk) {
   Frags f;
-  f.r = rsrc(p, unsigned(N) * unsigned(K) * 2u);
+  f.tile = unsigned(nblk) * 2048u;
+  f.r = rsrc(p, unsigned(N / 16) * f.tile);
   f.voff = unsigned(threadIdx.x & 63) * 16u;
-  f.tile = unsigned(K / 32) * 1024u;
   return f;
 }
 
@@ -288,8 +291,8 @@ __global__ __launch_bounds__(64 * NW) void cell_wide(StepArgs a) {
   constexpr int UN = 64 / G;  // hidden units of the tile
   constexpr int SCR = (RT + NB) * kSlot;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int B = a.B, D = a.D, H = a.H, GH = G * H, K1 = D + H;
-  const int mg = (B + TM - 1) / TM, ntile = mg * (H / UN);
+  const int B = a.B, D = a.D, H = a.H, GH = G * H;
+  const int mg = (B + TM - 1) / TM, ntile = mg * ((H + UN - 1) / UN);
   const int w = tile_of(ntile);
   if (w >= ntile) return;  // grid padding (the whole workgroup leaves together)
   const int m0 = (w % mg) * TM, j0 = (w / mg) * UN;
@@ -304,17 +307,29 @@ __global__ __launch_bounds__(64 * NW) void cell_wide(StepArgs a) {
       for (int nb = 0; nb < NB; ++nb) acc[i][nb] = f4{0.f, 0.f, 0.f, 0.f};
     Xpose X;
     X.init();
-    const int nbk = K1 / 64, nbx = D / 64;
+    const int nbx = blocks(D), nbk = nbx + blocks(H);
     const int c0 = (nbk * wave) / NW, c1 = (nbk * (wave + 1)) / NW;
-    const Rows xs = rows_of(a.x, unsigned(size_t(B) * D * 2), m0, 2 * D);  // < 4 GiB: cell_wide_fits
-    const Rows hs = rows_of(a.h, unsigned(size_t(B) * H * 2), m0, 2 * H);
-    const Frags wf = frags_of(a.W, GH, K1);
+    const unsigned xbytes = unsigned(size_t(B) * D * 2), hbytes = unsigned(size_t(B) * H * 2);  // < 4 GiB: cell_wide_fits
+    const Rows xs = rows_of(a.x, xbytes, m0, D), hs = rows_of(a.h, hbytes, m0, H);
+    const Frags wf = frags_of(a.W, GH, nbk);
     nt_rows<RT, NB, S, true>(
         c0, c1, lds + wave * SCR, X, acc,
-        [&](int g, int h, int blk) -> u4v {  // an x or an h block: the same choice for the whole wave
-          return blk < nbx ? xs.load(g, h, blk) : hs.load(g, h, blk - nbx);
+        [&](int g, int h, int blk) -> u4v {
+          // an x or an h block: the same choice for the whole wave, made by
+          // selects (with branches around the loads a step of the 2048-LSTM
+          // took 19.6 us instead of 16.2)
+          const bool inx = blk < nbx;
+          const int bk = inx ? blk : blk - nbx;
+          const unsigned v = inx ? xs.voff : hs.voff, vt = inx ? xs.vtail : hs.vtail;
+          const unsigned long long p = inx ? (unsigned long long)a.x : (unsigned long long)a.h;
+          return bload(__builtin_amdgcn_make_buffer_rsrc((void*)p, 0, inx ? xbytes : hbytes, 0x00020000),
+                       bk == (inx ? xs.half : hs.half) ? vt : v,
+                       (inx ? xs.base : hs.base) + unsigned(16 * g + 8 * h) * (inx ? xs.stride : hs.stride) +
+                           unsigned(bk) * 128u);
         },
-        [&](int g, int c, int blk) -> u4v { return wf.load(((16 * g / UN) * H + j0 + (16 * g) % UN) / 16, 2 * blk + c); });
+        [&](int g, int c, int blk) -> u4v {  // units past H (the tanh RNN's last tile): the last 16 again, unused
+          return wf.load((16 * g / UN) * (H / 16) + min((j0 + (16 * g) % UN) / 16, H / 16 - 1), 2 * blk + c);
+        });
     __syncthreads();  // every wave has left its scratch
     put_partials<RT, NB>(ps, wave, acc);
   }
@@ -326,7 +341,7 @@ __global__ __launch_bounds__(64 * NW) void cell_wide(StepArgs a) {
 #pragma clang fp contract(on)  // the same bits with and without the gate product
     const int ml = pi / UN, u = pi % UN;
     const int m = m0 + ml, j = j0 + u;
-    if (m >= B) continue;
+    if (m >= B || j >= H) continue;
     const int o = m * H + j;
     float z[G];
 #pragma unroll
@@ -451,14 +466,14 @@ __device__ __forceinline__ void prod_tile(const ProdArgs& a, int m0, int n0, cha
   for (int i = 0; i < RT; ++i)
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[i][nb] = f4{0.f, 0.f, 0.f, 0.f};
-  const int nbk = K / 64;
+  const int nbk = blocks(K);
   const int c0 = (nbk * wave) / NW, c1 = (nbk * (wave + 1)) / NW;
   Xpose X;
   X.init();
   char* scr = lds + wave * SCR;
-  const Rows as = rows_of(a.A, unsigned(size_t(M) * K * 2), m0, 2 * K);  // < 4 GiB: the fits checks
+  const Rows as = rows_of(a.A, unsigned(size_t(M) * K * 2), m0, K);  // < 4 GiB: the fits checks
   if constexpr (!NN) {
-    const Frags bf = frags_of(a.B, N, K);
+    const Frags bf = frags_of(a.B, N, nbk);
     nt_rows<RT, NB, S, true>(
         c0, c1, scr, X, acc, [&](int g, int h, int blk) -> u4v { return as.load(g, h, blk); },
         [&](int g, int c, int blk) -> u4v { return bf.load(n0 / 16 + g, 2 * blk + c); });
@@ -468,7 +483,8 @@ __device__ __forceinline__ void prod_tile(const ProdArgs& a, int m0, int n0, cha
     // nn_swz(t), and a fragment (column l & 15 of a 16-column segment, 8 consecutive k) comes back with two
     // transposing reads (nn_frag).
     const int lane = tid & 63;
-    const Rows bs = rows_of(a.B, unsigned(size_t(K) * N * 2), 0, 2 * N);
+    // (rows k past K read zero, columns past N something whose results are unused)
+    const Rows bs = rows_of(a.B, unsigned(size_t(K) * N * 2), 0, N);
     const unsigned bcol = unsigned(n0) * 2u;
     char* bt = scr + RT * kSlot;
     const int lr = lane >> 3, lp = lane & 7;  // row within the instruction, 16-byte piece of the row
@@ -516,7 +532,7 @@ template <int RT, int NB, bool NN, int NW = kWaves, int S = NN ? 2 : (RT * NB >=
 __global__ __launch_bounds__(64 * NW) void prod_wide(ProdArgs a) {
   constexpr int TM = 16 * RT, TN = 16 * NB;
   const int tid = threadIdx.x, M = a.M, N = a.N;
-  const int mg = (M + TM - 1) / TM, ntile = mg * (N / TN);
+  const int mg = (M + TM - 1) / TM, ntile = mg * ((N + TN - 1) / TN);
   const int w = tile_of(ntile);
   if (w >= ntile) return;
   const int m0 = (w % mg) * TM, n0 = (w / mg) * TN;
@@ -526,7 +542,7 @@ __global__ __launch_bounds__(64 * NW) void prod_wide(ProdArgs a) {
   for (int pi = tid; pi < TM * TN; pi += 64 * NW) {
     const int ml = pi / TN, nl = pi % TN;
     const int m = m0 + ml;
-    if (m >= M) continue;
+    if (m >= M || n0 + nl >= N) continue;
     const float s = sum_partials<RT, NB, NW>(ps, ml, nl);
     const size_t o = (size_t)m * N + n0 + nl;
     a.out[o] = a.add ? a.add[o] + s : s;
@@ -550,7 +566,7 @@ __device__ __forceinline__ void mlp_epilogue(const MlpArgs& a, int tile, int m0,
 #pragma clang fp contract(on)  // the same bits with and without the product
     const int ml = pi / TN, nl = pi % TN;
     const int m = m0 + ml, c = n0 + nl;
-    if (m >= B) continue;
+    if (m >= B || c >= w) continue;
     const size_t o = (size_t)m * w + c;
     const float z = CACHED ? a.zc_in[o] : zsum(ml, nl) + a.bias[c];
     if (MODE == kForward && a.zc_out) a.zc_out[o] = z;
@@ -604,7 +620,7 @@ __global__ __launch_bounds__(64 * NW) void mlp_wide(MlpArgs a) {
   constexpr int SCR = (RT + NB) * kSlot;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int B = a.B, w = a.w;
-  const int mg = (B + TM - 1) / TM, ntile = mg * (w / TN);
+  const int mg = (B + TM - 1) / TM, ntile = mg * ((w + TN - 1) / TN);
   const int tile = tile_of(ntile);
   if (tile >= ntile) return;
   const int m0 = (tile % mg) * TM, n0 = (tile / mg) * TN;
@@ -619,10 +635,10 @@ __global__ __launch_bounds__(64 * NW) void mlp_wide(MlpArgs a) {
       for (int nb = 0; nb < NB; ++nb) acc[i][nb] = f4{0.f, 0.f, 0.f, 0.f};
     Xpose X;
     X.init();
-    const int nbk = w / 64;
+    const int nbk = blocks(w);
     const int c0 = (nbk * wave) / NW, c1 = (nbk * (wave + 1)) / NW;
-    const Rows ys = rows_of(a.y, unsigned(size_t(B) * w * 2), m0, 2 * w);  // < 4 GiB: mlp_wide_fits
-    const Rows ws = rows_of(a.W, unsigned(size_t(w) * w * 2), n0, 2 * w);
+    const Rows ys = rows_of(a.y, unsigned(size_t(B) * w * 2), m0, w);  // < 4 GiB: mlp_wide_fits
+    const Rows ws = rows_of(a.W, unsigned(size_t(w) * w * 2), n0, w);
     nt_rows<RT, NB, S>(
         c0, c1, lds + wave * SCR, X, acc, [&](int g, int h, int blk) -> u4v { return ys.load(g, h, blk); },
         [&](int g, int h, int blk) -> u4v { return ws.load(g, h, blk); });
@@ -641,7 +657,7 @@ __global__ __launch_bounds__(64 * NW) void mlp_wide(MlpArgs a) {
 template <int RT, int NW = kWaves>
 __global__ __launch_bounds__(64 * NW) void mlp_back_wide(MlpArgs a) {
   constexpr int TM = 16 * RT;
-  const int mg = (a.B + TM - 1) / TM, ntile = mg * (a.w / 64);
+  const int mg = (a.B + TM - 1) / TM, ntile = mg * ((a.w + 63) / 64);
   const int tile = tile_of(ntile);
   if (tile >= ntile) return;
   const int m0 = (tile % mg) * TM, n0 = (tile / mg) * 64;
@@ -671,42 +687,55 @@ int row_tiles(int M, int cols) { return (M + 16 * tile_rows(M, cols) - 1) / (16 
 
 unsigned grid_for(int ntile) { return unsigned(8 * ((ntile + 7) / 8)); }
 
-// dst (fragment order, Frags) <- the [N][K] rows of src (row stride ld): one
-// thread per 16-byte lane chunk, written in order.
-__global__ __launch_bounds__(256) void pack_nt(const char* __restrict__ src, int K, int ld, size_t chunks,
+// dst (fragment order, Frags) <- the [N][K0 + K1] rows of src (row stride ld),
+// the two segments each padded to whole blocks: one thread per 16-byte lane
+// chunk, written in order.
+__global__ __launch_bounds__(256) void pack_nt(const char* __restrict__ src, int K0, int K1, int ld, size_t chunks,
                                                char* __restrict__ dst) {
   const size_t t = size_t(blockIdx.x) * 256 + threadIdx.x;
   if (t >= chunks) return;
-  const int l = int(t & 63);
-  const size_t f = t >> 6, kf = size_t(K / 32);
-  const size_t jt = f / kf, ks = f % kf;
-  const size_t row = 16 * jt + size_t(l & 15), col = 32 * ks + 8 * size_t(l >> 4);
-  *(u4v*)(dst + 16 * t) = *(const u4v*)(src + 2 * (row * size_t(ld) + col));
+  const int l = int(t & 63), b0 = blocks(K0);
+  const size_t f = t >> 6, kf = 2 * size_t(b0 + blocks(K1));
+  const size_t jt = f / kf;
+  const int ks = int(f % kf);
+  const bool first = ks < 2 * b0;
+  const int k = 32 * (first ? ks : ks - 2 * b0) + 8 * (l >> 4);  // within the segment
+  u4v v = {0u, 0u, 0u, 0u};
+  if (k < (first ? K0 : K1)) {
+    const size_t row = 16 * jt + size_t(l & 15);
+    v = *(const u4v*)(src + 2 * (row * size_t(ld) + size_t(first ? k : K0 + k)));
+  }
+  *(u4v*)(dst + 16 * t) = v;
 }
 
 }  // namespace
 
-hipError_t launch_pack_nt_bf16(const void* src, int N, int K, int ld, void* dst, hipStream_t s) {
-  if (N < 16 || N % 16 != 0 || K < 32 || K % 32 != 0 || ld < K || ld % 8 != 0 ||
-      size_t(N) * size_t(K) * 2 > 0xFFFFFFFFull)  // Frags addresses the copy with 32-bit offsets
+size_t pack_nt_bytes(int N, int K0, int K1) { return size_t(N / 16) * size_t(blocks(K0) + blocks(K1)) * 2048; }
+
+hipError_t launch_pack_nt_bf16(const void* src, int N, int K0, int K1, int ld, void* dst, hipStream_t s) {
+  const size_t bytes = pack_nt_bytes(N, K0, K1);
+  if (N < 16 || N % 16 != 0 || K0 < 0 || K1 < 32 || K0 % 32 != 0 || K1 % 32 != 0 || ld < K0 + K1 || ld % 8 != 0 ||
+      bytes > 0xFFFFFFFFull)  // Frags addresses the copy with 32-bit offsets
     return hipErrorInvalidValue;
-  const size_t chunks = size_t(N) * size_t(K) / 8;
-  hipLaunchKernelGGL(pack_nt, dim3(unsigned((chunks + 255) / 256)), dim3(256), 0, s, (const char*)src, K, ld, chunks,
+  const size_t chunks = bytes / 16;
+  hipLaunchKernelGGL(pack_nt, dim3(unsigned((chunks + 255) / 256)), dim3(256), 0, s, (const char*)src, K0, K1, ld, chunks,
                      (char*)dst);
   return hipGetLastError();
 }
 
 // Every operand is addressed with 32-bit buffer offsets: each must stay under 4 GiB.
-static bool under_4g(size_t rows, size_t cols) { return rows * cols * 2 <= 0xFFFFFFFFull; }
+static bool under_4g(size_t rows, size_t cols) { return rows * (cols + 128) * 2 <= 0xFFFFFFFFull; }
 
 bool cell_wide_fits(int G, int B, int D, int H) {
-  return D % 64 == 0 && H % 64 == 0 && H > 0 && B > 0 && under_4g(size_t(B), size_t(D) + size_t(H)) &&
-         under_4g(size_t(G) * H, size_t(D) + size_t(H)) && under_4g(size_t(B), size_t(G) * H);
+  return D % 32 == 0 && H % 32 == 0 && H > 0 && B > 0 && under_4g(size_t(B), size_t(D) + size_t(H)) &&
+         under_4g(size_t(G) * H, size_t(D) + size_t(H)) && under_4g(size_t(B), size_t(G) * H) &&
+         under_4g(size_t(H), size_t(G) * H);
 }
 
-bool mlp_wide_fits(int B, int w) { return w % 64 == 0 && w > 0 && B > 0 && under_4g(size_t(w), size_t(w)) && under_4g(size_t(B), size_t(w)); }
+bool mlp_wide_fits(int B, int w) { return w % 32 == 0 && w > 0 && B > 0 && under_4g(size_t(w) + 64, size_t(w)) && under_4g(size_t(B), size_t(w)); }
 
-int cell_wide_tiles(int G, int B, int H) { return row_tiles(B, H / (64 / G)) * (H / (64 / G)); }
+static int cell_cols(int G, int H) { return (H + 64 / G - 1) / (64 / G); }
+int cell_wide_tiles(int G, int B, int H) { return row_tiles(B, cell_cols(G, H)) * cell_cols(G, H); }
 
 template <int G, int RT>
 static hipError_t launch_cell_wide_rt(int mode, const StepArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
@@ -719,7 +748,7 @@ static hipError_t launch_cell_wide_rt(int mode, const StepArgs& a, hipStream_t s
 
 template <int G>
 static hipError_t launch_cell_wide_g(int mode, const StepArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  switch (tile_rows(a.B, a.H / (64 / G))) {
+  switch (tile_rows(a.B, cell_cols(G, a.H))) {
     case 4: return launch_cell_wide_rt<G, 4>(mode, a, s, e0, e1);
     case 2: return launch_cell_wide_rt<G, 2>(mode, a, s, e0, e1);
     default: return launch_cell_wide_rt<G, 1>(mode, a, s, e0, e1);
@@ -734,7 +763,7 @@ hipError_t launch_cell_wide(int G, int mode, const StepArgs& a, hipStream_t s, h
 bool prod_wide_big(int M, int N) { return N % 32 == 0 && ((M + 31) / 32) * (N / 32) >= 192; }
 
 hipError_t launch_prod_nt(const ProdArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  if (a.K % 64 != 0 || a.N % 16 != 0 || a.M < 1) return hipErrorInvalidValue;
+  if (a.K % 32 != 0 || a.N % 16 != 0 || a.M < 1) return hipErrorInvalidValue;
   const dim3 block(64 * kWaves);
   if (prod_wide_big(a.M, a.N)) {
     const dim3 grid(grid_for(((a.M + 31) / 32) * (a.N / 32)));
@@ -746,12 +775,12 @@ hipError_t launch_prod_nt(const ProdArgs& a, hipStream_t s, hipEvent_t e0, hipEv
   return hipGetLastError();
 }
 
-int mlp_wide_tiles(int B, int w) { return row_tiles(B, w / 64) * (w / 64); }
+int mlp_wide_tiles(int B, int w) { return row_tiles(B, blocks(w)) * blocks(w); }
 
 hipError_t launch_prod_nn(const ProdArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  if (a.K % 64 != 0 || a.N % 64 != 0 || a.M < 1) return hipErrorInvalidValue;
+  if (a.K % 32 != 0 || a.N % 32 != 0 || a.M < 1) return hipErrorInvalidValue;
   const dim3 grid(grid_for(mlp_wide_tiles(a.M, a.N))), block(64 * kWaves);
-  switch (tile_rows(a.M, a.N / 64)) {
+  switch (tile_rows(a.M, blocks(a.N))) {
     case 4: hipExtLaunchKernelGGL((prod_wide<4, 4, true>), grid, block, 0, s, e0, e1, 0, a); break;
     case 2: hipExtLaunchKernelGGL((prod_wide<2, 4, true>), grid, block, 0, s, e0, e1, 0, a); break;
     default: hipExtLaunchKernelGGL((prod_wide<1, 4, true>), grid, block, 0, s, e0, e1, 0, a); break;
@@ -769,7 +798,7 @@ static hipError_t launch_mlp_wide_rt(int mode, const MlpArgs& a, hipStream_t s, 
 }
 
 static hipError_t launch_mlp_wide_any(int mode, const MlpArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  switch (tile_rows(a.B, a.w / 64)) {
+  switch (tile_rows(a.B, blocks(a.w))) {
     case 4: return launch_mlp_wide_rt<4>(mode, a, s, e0, e1);
     case 2: return launch_mlp_wide_rt<2>(mode, a, s, e0, e1);
     default: return launch_mlp_wide_rt<1>(mode, a, s, e0, e1);
