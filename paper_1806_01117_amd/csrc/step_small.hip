@@ -71,7 +71,7 @@ struct Op<__bf16> {
 };
 
 constexpr int kWaves = 8;
-constexpr int kU = 4;  // chunks per prefetch group
+constexpr int kU = 2;  // chunks per prefetch group
 
 // acc[nb] += sum over chunks [c0, c1) of a(ch) . b(ch, nb); loads run one group
 // of kU chunks ahead of the MFMAs.
