@@ -19,9 +19,17 @@
 // output; W_h is read through its transpose WhT[j][k] = W[k][D+j] so both
 // products are row-contiguous in the reduction index.
 //
-// Operands are fp32 (v_mfma_f32_16x16x4_f32, chunks of 16 reduction indices,
-// 4 per lane) or bf16 (v_mfma_f32_16x16x32_bf16, chunks of 32, 8 per lane):
-// either way a lane loads 16 bytes per operand row per chunk.  With bf16 the
+// Loads.  A vector load costs by the 128-byte lines it touches, so one
+// instruction reads 8 rows x 128 bytes (lane l: row l >> 3, bytes 16 (l & 7))
+// of W, [x | h], zbar or W_h^T where the reduction is long, not the MFMA
+// operand's 16 rows x 64 bytes (kept for short ones); each
+// wave turns its rows into fragments through swizzled LDS tiles of its own (no
+// workgroup barrier in the loop).  A row of x or h (and the weights' part that
+// meets it) that ends in the middle of a 128-byte block reads zeros after it.
+//
+// Operands are fp32 (v_mfma_f32_16x16x4_f32, 4 per 16 bytes of a lane) or bf16
+// (v_mfma_f32_16x16x32_bf16, one per 16 bytes): either way a block is 128
+// bytes of an operand row, two fragments.  With bf16 the
 // stored h, the copy of h_t for the weight gradient and zbar (the adjoint
 // GEMMs' operand) are rounded to bf16 (nearest even); accumulation, the cell
 // state and its adjoint stay fp32.
@@ -117,19 +125,77 @@ __device__ __forceinline__ void chunks(int c0, int c1, f4 (&acc)[NB], LA la, LB 
   }
 }
 
+constexpr int kS = 2;          // blocks of loads in flight per wave
+constexpr int kTile = 2048;    // one 16-row x 128-byte scratch tile
+constexpr unsigned kPast = 0x7f000000u;  // an offset past any Rows8
+
+typedef unsigned int u4v __attribute__((ext_vector_type(4)));
+
+// Eight consecutive rows of an operand from `base` on (bytes past the last
+// row read zero); `stride` bytes from row to row.
+struct Rows8 {
+  unsigned long long base;
+  unsigned bytes;
+  __device__ __forceinline__ u4v load(unsigned voff, unsigned soff) const {
+    return __builtin_amdgcn_raw_buffer_load_b128(
+        __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000), voff, soff, 0);
+  }
+};
+__device__ __forceinline__ Rows8 rows8(const void* p, size_t row0, int rows, size_t stride) {
+  const unsigned long long q = (unsigned long long)p + row0 * stride;
+  const unsigned lo = __builtin_amdgcn_readfirstlane(unsigned(q)), hi = __builtin_amdgcn_readfirstlane(unsigned(q >> 32));
+  return {((unsigned long long)hi << 32) | lo,
+          unsigned(__builtin_amdgcn_readfirstlane(unsigned(size_t(max(0, min(rows, 8))) * stride)))};
+}
+
+// acc[nb] += the wave's blocks [c0, c1) of A (16 rows) and B (16 rows per
+// column block nb).  ld(blk, v) loads a block's 2 + 2 NB pieces of 8 rows: A's
+// rows 0-7 and 8-15, then B's.
+template <class T, int NB, class LD>
+__device__ __forceinline__ void blocks(int c0, int c1, char* scr, f4 (&acc)[NB], LD ld) {
+  using V = typename Op<T>::V;
+  if (c0 >= c1) return;
+  const int lane = threadIdx.x & 63, t = lane >> 3, k = lane & 7, r = lane & 15, q = lane >> 4;
+  // row t's 16-byte piece k lies in slot k ^ (t & 7) of the row
+  const int w0 = t * 128 + 16 * (k ^ t), r0 = r * 128 + 16 * (q ^ (r & 7)), r1 = r * 128 + 16 * ((q + 4) ^ (r & 7));
+  u4v v[kS][2 + 2 * NB];
+#pragma unroll
+  for (int s = 0; s < kS; ++s) ld(min(c0 + s, c1 - 1), v[s]);
+  for (int c = c0; c < c1; c += kS) {
+#pragma unroll
+    for (int s = 0; s < kS; ++s) {
+      if (c + s >= c1) break;
+#pragma unroll
+      for (int i = 0; i < 2 + 2 * NB; ++i) *(u4v*)(scr + (i >> 1) * kTile + (i & 1) * 1024 + w0) = v[s][i];
+      if (c + s + kS < c1) ld(c + s + kS, v[s]);
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const V a = *(const V*)(scr + (h ? r1 : r0));
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[nb] = Op<T>::mma(a, *(const V*)(scr + (1 + nb) * kTile + (h ? r1 : r0)), acc[nb]);
+      }
+      __builtin_amdgcn_wave_barrier();  // the tiles are read before the next block is stored
+    }
+  }
+}
+
 // CACHED (adjoint): the step's pre-activations are kept (a.zc_in) and its
 // gate product is not formed again.
-template <class T, int G, int MODE, bool CACHED = false>
+// RG, RH: the gate product's and the h-adjoint product's loads go by rows
+// through LDS (blocks), else by fragments (chunks).
+template <class T, int G, int MODE, bool RG, bool RH, bool CACHED>
 __global__ __launch_bounds__(64 * kWaves) void step_small(StepArgs a) {
+  constexpr size_t E = sizeof(T);
   using V = typename Op<T>::V;
-  constexpr int CW = Op<T>::CW;
-  constexpr int LE = CW / 4;  // elements per lane per chunk (16 bytes)
+  constexpr int CW = Op<T>::CW, LE = CW / 4;  // a chunk's elements, a lane's (16 bytes)
   constexpr int U = (G == 4) ? 8 : 16;  // units per workgroup
   constexpr int NC = G * U;             // gate columns (32 or 16)
   constexpr int NB = NC / 16;           // MFMA column blocks
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, q = lane >> 4;
   const int B = a.B, D = a.D, H = a.H, GH = G * H, K1 = D + H;
+  const unsigned lrow = lane >> 3, lpiece = 16 * (lane & 7);  // this lane's row and bytes of a load
   // XCD-aware tile order.  Workgroups are dealt to the 8 XCDs round-robin by
   // id, so ids with equal id % 8 share an L2.  Tiles are numbered unit-group
   // major (w = ug * mtiles + mt) and each XCD takes a contiguous run of them:
@@ -141,31 +207,60 @@ __global__ __launch_bounds__(64 * kWaves) void step_small(StepArgs a) {
   const int m0 = (w % mtiles) * 16;
   const int j0 = (w / mtiles) * U;
   const int wg_slot = w;   // loss accumulator of this tile
-  const int row = min(m0 + r, B - 1);  // rows >= B: clamped loads, results dropped
+  const int row = min(m0 + r, B - 1);  // chunks: rows >= B are loaded clamped, their results dropped
 
   __shared__ float zs[CACHED ? 1 : kWaves][16][NC + 1];
   __shared__ float hs[kWaves][16][17];
+  __shared__ __attribute__((aligned(16))) char scratch[RG || RH ? kWaves : 1][(1 + NB) * kTile];
+  char* scr = scratch[RG || RH ? wave : 0];
 
   if (MODE != kFinal && !CACHED) {
     f4 acc[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[nb] = f4{0.f, 0.f, 0.f, 0.f};
-    const int nch = K1 / CW;
-    const int c0 = (nch * wave) / kWaves, c1 = (nch * (wave + 1)) / kWaves;
-    const T* xr = (const T*)a.x + (size_t)row * D;
-    const T* hr = (const T*)a.h + (size_t)row * H;
-    const T* wr[NB];
+    if constexpr (RG) {
+      // blocks of x, then of h
+      const unsigned xrow = unsigned(D * E), hrow = unsigned(H * E), wrow = xrow + hrow;  // row bytes
+      const int nx = int(xrow + 127) / 128, nblk = nx + int(hrow + 127) / 128;
+      const int c0 = (nblk * wave) / kWaves, c1 = (nblk * (wave + 1)) / kWaves;
+      const int xh = xrow % 128 ? nx - 1 : -1, hh = hrow % 128 ? nblk - 1 : -1;  // blocks that end in the middle
+      const Rows8 xr[2] = {rows8(a.x, m0, B - m0, xrow), rows8(a.x, m0 + 8, B - m0 - 8, xrow)};
+      const Rows8 hr[2] = {rows8(a.h, m0, B - m0, hrow), rows8(a.h, m0 + 8, B - m0 - 8, hrow)};
+      Rows8 wr[2 * NB];  // 8 columns: the LSTM's units of one gate, or half the RNN's units
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const int n = nb * 16 + r;  // column of this lane in block nb
-      wr[nb] = (const T*)a.W + (size_t)((n / U) * H + j0 + (n % U)) * K1;
+      for (int i = 0; i < 2 * NB; ++i) wr[i] = rows8(a.W, G == 4 ? size_t(i) * H + j0 : size_t(j0 + 8 * i), 8, wrow);
+      const unsigned xv = lrow * xrow + lpiece, hv = lrow * hrow + lpiece, wv = lrow * wrow + lpiece;
+      blocks<T, NB>(c0, c1, scr, acc, [&](int blk, u4v* v) {
+        const bool inx = blk < nx;  // selects, not branches: the same for the whole wave
+        const bool cut = (blk == xh || blk == hh) && lpiece >= 64;
+        const unsigned so = unsigned(inx ? blk : blk - nx) * 128u;
+        const unsigned av = cut ? kPast : inx ? xv : hv, bv = cut ? kPast : wv;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const Rows8 s{inx ? xr[i].base : hr[i].base, inx ? xr[i].bytes : hr[i].bytes};
+          v[i] = s.load(av, so);
+        }
+#pragma unroll
+        for (int i = 0; i < 2 * NB; ++i) v[2 + i] = wr[i].load(bv, so + (inx ? 0u : xrow));
+      });
+    } else {
+      const int nch = K1 / CW;
+      const int c0 = (nch * wave) / kWaves, c1 = (nch * (wave + 1)) / kWaves;
+      const T* xr = (const T*)a.x + (size_t)row * D;
+      const T* hr = (const T*)a.h + (size_t)row * H;
+      const T* wr[NB];
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const int n = nb * 16 + r;  // column of this lane in block nb
+        wr[nb] = (const T*)a.W + (size_t)((n / U) * H + j0 + (n % U)) * K1;
+      }
+      chunks<T, NB>(c0, c1, acc,
+                    [&](int ch) -> V {
+                      const int k = ch * CW + LE * q;
+                      return *(const V*)(ch * CW < D ? xr + k : hr + (k - D));
+                    },
+                    [&](int ch, int nb) -> V { return *(const V*)(wr[nb] + ch * CW + LE * q); });
     }
-    chunks<T, NB>(c0, c1, acc,
-                  [&](int ch) -> V {
-                    const int k = ch * CW + LE * q;
-                    return *(const V*)(ch * CW < D ? xr + k : hr + (k - D));
-                  },
-                  [&](int ch, int nb) -> V { return *(const V*)(wr[nb] + ch * CW + LE * q); });
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -174,13 +269,30 @@ __global__ __launch_bounds__(64 * kWaves) void step_small(StepArgs a) {
   const bool do_hbar = (MODE == kFinal) || (MODE == kAdjoint && !a.first);
   if (do_hbar) {
     f4 acc[1] = {f4{0.f, 0.f, 0.f, 0.f}};
-    const int nch = GH / CW;
-    const int c0 = (nch * wave) / kWaves, c1 = (nch * (wave + 1)) / kWaves;
-    const T* zr = (const T*)a.zbar_in + (size_t)row * GH;
-    // U units; lanes r >= U (LSTM) repeat units so no extra rows are fetched
-    const T* wt = (const T*)a.WhT + (size_t)(j0 + (r % U)) * GH;
-    chunks<T, 1>(c0, c1, acc, [&](int ch) -> V { return *(const V*)(zr + ch * CW + LE * q); },
-                 [&](int ch, int) -> V { return *(const V*)(wt + ch * CW + LE * q); });
+    if constexpr (RH) {
+      const unsigned zrow = unsigned(GH * E);
+      const int nblk = int(zrow + 127) / 128, zh = zrow % 128 ? nblk - 1 : -1;
+      const int c0 = (nblk * wave) / kWaves, c1 = (nblk * (wave + 1)) / kWaves;
+      const Rows8 zr[2] = {rows8(a.zbar_in, m0, B - m0, zrow), rows8(a.zbar_in, m0 + 8, B - m0 - 8, zrow)};
+      // U units: 8 (columns 8 .. 15 of the product are unused) or 16
+      const Rows8 tr[2] = {rows8(a.WhT, j0, 8, zrow), rows8(a.WhT, j0 + 8, U == 16 ? 8 : 0, zrow)};
+      const unsigned zv = lrow * zrow + lpiece;
+      blocks<T, 1>(c0, c1, scr, acc, [&](int blk, u4v* v) {
+        const unsigned vo = blk == zh && lpiece >= 64 ? kPast : zv, so = unsigned(blk) * 128u;
+        v[0] = zr[0].load(vo, so);
+        v[1] = zr[1].load(vo, so);
+        v[2] = tr[0].load(vo, so);
+        v[3] = U == 16 ? tr[1].load(vo, so) : u4v{0u, 0u, 0u, 0u};
+      });
+    } else {
+      const int nch = GH / CW;
+      const int c0 = (nch * wave) / kWaves, c1 = (nch * (wave + 1)) / kWaves;
+      const T* zr = (const T*)a.zbar_in + (size_t)row * GH;
+      // U units; lanes r >= U (LSTM) repeat units so no extra rows are fetched
+      const T* wt = (const T*)a.WhT + (size_t)(j0 + (r % U)) * GH;
+      chunks<T, 1>(c0, c1, acc, [&](int ch) -> V { return *(const V*)(zr + ch * CW + LE * q); },
+                   [&](int ch, int) -> V { return *(const V*)(wt + ch * CW + LE * q); });
+    }
 #pragma unroll
     for (int v = 0; v < 4; ++v) hs[wave][4 * q + v][r] = acc[0][v];
   }
@@ -295,26 +407,45 @@ hipError_t launch_step_small(int G, int bf16, int mode, const StepArgs& a, hipSt
                              hipEvent_t e1) {
   dim3 grid, block;
   step_small_grid(G, a.B, a.H, &grid, &block);
-#define AMB_L(T_, G_, ...) hipExtLaunchKernelGGL((step_small<T_, G_, __VA_ARGS__>), grid, block, 0, s, e0, e1, 0, a)
-#define AMB_T(T_)                                   \
-  if (G == 4) {                                     \
-    if (mode == kForward) AMB_L(T_, 4, kForward);   \
-    else if (mode == kAdjoint && a.zc_in) AMB_L(T_, 4, kAdjoint, true); \
-    else if (mode == kAdjoint) AMB_L(T_, 4, kAdjoint); \
-    else AMB_L(T_, 4, kFinal);                      \
-  } else {                                          \
-    if (mode == kForward) AMB_L(T_, 1, kForward);   \
-    else if (mode == kAdjoint && a.zc_in) AMB_L(T_, 1, kAdjoint, true); \
-    else if (mode == kAdjoint) AMB_L(T_, 1, kAdjoint); \
-    else AMB_L(T_, 1, kFinal);                      \
-  }
+  // By rows where the reduction is long enough (128-byte blocks of it): with
+  // one or two blocks per wave the trip through LDS costs more than the lines
+  // it saves.  Forward by rows / by fragments: 40 blocks (32 x 1024, D 256, fp32)
+  // 9.5 / 11.5 us, 30 (tanh RNN, 64 x 896) 6.9 / 7.0, 17.5 (16 x 544) 7.1 / 6.6,
+  // 9 (5 x 80) 6.2 / 5.7.  Adjoint, h-adjoint product: 128 blocks 14.6 / 21.0,
+  // 32 (20 x 512, bf16) 6.0 / 8.4, 16 (40 x 256, bf16) 5.4 / 6.0, 10 (5 x 80)
+  // 6.6 / 6.2.
+  const size_t e = bf16 ? 2 : 4;
+  const bool rg = size_t(a.D + a.H) * e >= 20 * 128, rh = size_t(G) * a.H * e >= 16 * 128;
+#define AMB_K(T_, G_, M_, RG_, RH_, C_) \
+  hipExtLaunchKernelGGL((step_small<T_, G_, M_, RG_, RH_, C_>), grid, block, 0, s, e0, e1, 0, a)
+#define AMB_T(T_, G_)                                                          \
+  do {                                                                         \
+    if (mode == kForward) {                                                    \
+      if (rg) AMB_K(T_, G_, kForward, true, false, false);                     \
+      else AMB_K(T_, G_, kForward, false, false, false);                       \
+    } else if (mode == kFinal) {                                               \
+      if (rh) AMB_K(T_, G_, kFinal, false, true, false);                       \
+      else AMB_K(T_, G_, kFinal, false, false, false);                         \
+    } else if (a.zc_in) {                                                      \
+      if (rh) AMB_K(T_, G_, kAdjoint, false, true, true);                      \
+      else AMB_K(T_, G_, kAdjoint, false, false, true);                        \
+    } else if (rg) {                                                           \
+      if (rh) AMB_K(T_, G_, kAdjoint, true, true, false);                      \
+      else AMB_K(T_, G_, kAdjoint, true, false, false);                        \
+    } else {                                                                   \
+      if (rh) AMB_K(T_, G_, kAdjoint, false, true, false);                     \
+      else AMB_K(T_, G_, kAdjoint, false, false, false);                       \
+    }                                                                          \
+  } while (0)
   if (bf16) {
-    AMB_T(__bf16)
+    if (G == 4) AMB_T(__bf16, 4);
+    else AMB_T(__bf16, 1);
   } else {
-    AMB_T(float)
+    if (G == 4) AMB_T(float, 4);
+    else AMB_T(float, 1);
   }
 #undef AMB_T
-#undef AMB_L
+#undef AMB_K
   return hipGetLastError();
 }
 
