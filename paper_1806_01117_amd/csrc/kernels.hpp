@@ -224,6 +224,7 @@ bool dw_f32_big_fits(const DwArgs& a);
 hipError_t launch_dw_f32_big(const DwArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 // The weight-gradient window on the bf16 matrix cores (dw_f32x3.hip).
 bool dw_f32x3_fits(const DwArgs& a);
+bool dw_f32x3_pays(const DwArgs& a);
 hipError_t launch_dw_f32x3(const DwArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 // Small-batch path: one launch per step, 16 rows x (8 LSTM | 16 RNN) units per workgroup.
 void step_small_grid(int G, int B, int H, dim3* grid, dim3* block);

@@ -1045,7 +1045,7 @@ struct Exec {
           [&](hipEvent_t e0, hipEvent_t e1) {
             return L.mlpv ? launch_mlpv_dw(grp, int(cnt), ws, e0, e1)
                    : p.dtype == AMBPTT_BF16 ? launch_dw_bf16(d, ws, e0, e1)
-                   : C->lds_gemm == 1 && dw_f32x3_fits(d) ? launch_dw_f32x3(d, ws, e0, e1)
+                   : C->lds_gemm == 1 && dw_f32x3_fits(d) && dw_f32x3_pays(d) ? launch_dw_f32x3(d, ws, e0, e1)
                                                            : launch_dw(d, ws, e0, e1);
           },
           ws);
