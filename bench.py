@@ -117,7 +117,8 @@ def mlp_layer_work(ws, B: int) -> tuple[dict, dict]:
     forward y_{l+1} = relu(y_l W_l^T + b_l); adjoint z-bar_l from the
     recomputed z_l, the seed and u = z-bar_{l+1} W_{l+1}, formed in the same
     launch (no u for the last layer), with the copy of y_l kept for the
-    weight gradient; the weight gradient of one layer."""
+    weight gradient; the weight gradient of one layer.  (The library's adjoint
+    reads its mask and forms u alone; the count is of the layer's own work.)"""
     n = len(ws) - 1
     f = {"fwd": 0.0, "adj": 0.0, "dw": 0.0}
     b = dict(f)
@@ -226,6 +227,14 @@ def lds_kernels(spec, knobs) -> tuple[bool, bool]:
     cell = mode > 0 and cell_fit and (mode == 2 or -(-B // 128) * (G * H // 128) >= 256)
     prod = mode > 0 and prod_fit and (mode == 2 or -(-B // 64) * (H // 64) >= 256)
     return cell, prod
+
+
+def split_f32(spec, knobs) -> bool:
+    """Whether the fp32 large-batch path forms its products on the bf16 matrix
+    cores, each operand split in three bf16 parts (the library's default:
+    "lds_gemm", "hadj_launch" and "prod_split" all 1)."""
+    k = dict(knobs)
+    return spec.dtype == "f32" and all(k.get(n, 1) == 1 for n in ("lds_gemm", "hadj_launch", "prod_split"))
 
 
 def prod_split_parts(spec, knobs) -> int:
@@ -721,6 +730,10 @@ def _measure(args, knobs, wl, spec, host_slots, pinned_cap, dev, dx, dW, db, dh,
     from paper_1806_01117_amd._lib import KERNEL_CLASSES
     peak = FP32_MFMA_PEAK_TFLOPS if wl.dtype == "f32" else BF16_MFMA_PEAK_TFLOPS
     wide = st["kernel_calls"][3] > 0
+    # six bf16 products in the place of an fp32 one: the bound is a sixth of the bf16 peak
+    split = split_f32(spec, knobs) and wide and wl.cell in ("rnn", "lstm")
+    if split:
+        peak = BF16_MFMA_PEAK_TFLOPS / 6.0
     if wl.cell == "mlp":
         fl, byts = mlp_layer_work(wl.layer_widths(), wl.batch)
     else:
@@ -745,14 +758,21 @@ def _measure(args, knobs, wl, spec, host_slots, pinned_cap, dev, dx, dW, db, dh,
         traffic = measured_traffic(wl.name, "resident_pass")
     else:
         flops = {k: fl[k] for k in ("fwd", "adj", "hadj", "dw") if k in fl}
-        cand = [k for k in tot if k in flops]
+        # an adjoint whose step's pre-activations are kept forms no gate product,
+        # and the class holds both kinds: its launches have no one flop count
+        cand = [k for k in tot if k in flops and k != "adj"]
         dom = max(cand, key=tot.get) if cand else "adj"
         small = spec.batch * spec.hidden < 1024 * 256 or wl.dtype == "bf16"
         lds_cell, lds_prod = lds_kernels(spec, knobs)
         if wl.cell == "mlp":
             names = {"fwd": "mlpv_gemm forward: layer product + relu (mean over layers)",
-                     "adj": "mlpv_gemm adjoint: zbar_{l+1} W_{l+1}, recompute, mask, seed (mean over layers)",
+                     "adj": "mlpv_gemm adjoint: zbar_{l+1} W_{l+1}, mask, seed (mean over layers)",
                      "dw": "mlpv_dw weight gradient of one layer (mean over layers)"}
+        elif split:
+            names = {"fwd": "cell_f32x3 forward: gate product + cell update (six bf16 products)",
+                     "adj": "cell_f32x3 / cell_back_f32x3 adjoint",
+                     "hadj": "prod_f32x3 h-adjoint product zbar W_h (six bf16 products)",
+                     "dw": "dw_f32x3 weight-gradient window (six bf16 products)"}
         elif wide and wl.dtype == "f32":
             parts = prod_split_parts(spec, knobs)
             hadj_kernel = (f"prod_split_f32 ({parts} parts)" if parts > 1 else
@@ -777,6 +797,8 @@ def _measure(args, knobs, wl, spec, host_slots, pinned_cap, dev, dx, dW, db, dh,
                      "dw": ("dw_bf16" if wl.dtype == "bf16" else "dw_lds_f32") + " weight-gradient window"}
         if wl.cell == "mlp":
             key = "mlpv_" + dom
+        elif split:
+            key = {"fwd": "cell_f32x3_fwd", "adj": "cell_f32x3_adj", "hadj": "prod_f32x3"}.get(dom, "dw_f32x3")
         elif wide and wl.dtype == "f32":
             key = {"fwd": "cell_gemm_f32_fwd" if lds_cell else "step_f32_fwd",
                    "adj": "cell_gemm_f32_adj" if lds_cell else "step_f32_adj",
