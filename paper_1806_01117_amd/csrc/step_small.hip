@@ -132,7 +132,9 @@ constexpr unsigned kPast = 0x7f000000u;  // an offset past any Rows8
 typedef unsigned int u4v __attribute__((ext_vector_type(4)));
 
 // Eight consecutive rows of an operand from `base` on (bytes past the last
-// row read zero); `stride` bytes from row to row.
+// row read zero); `stride` bytes from row to row.  The range check takes the
+// sum of a load's two offsets, without wrapping: rows that are all past the
+// batch (no bytes) read zero at any offset.
 struct Rows8 {
   unsigned long long base;
   unsigned bytes;
