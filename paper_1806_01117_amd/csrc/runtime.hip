@@ -165,7 +165,7 @@ bool wide_pays(const ambptt_problem* p) {
   return weights >= double(1 << 21);
 }
 
-Layout make_layout(const ambptt_problem* p, int window, bool small_wide = true) {
+Layout make_layout(const ambptt_problem* p, int window, bool any_wide = true) {
   Layout L;
   L.G = p->cell == AMBPTT_CELL_LSTM ? 4 : 1;
   L.dsize = p->dtype == AMBPTT_BF16 ? 2 : 4;
@@ -195,7 +195,10 @@ Layout make_layout(const ambptt_problem* p, int window, bool small_wide = true) 
     resmlp_grid(p->batch, p->hidden, &grid, &block);
     L.loss_slots = int(grid.x * grid.y);
   }
-  if (p->dtype == AMBPTT_BF16 && (small_wide || p->batch >= 48) && wide_pays(p) &&
+  // 48 rows and more in whole 64-wide blocks take the wide kernels whatever
+  // their workspace; the others only if it costs them no call (below)
+  const bool whole = p->batch >= 48 && p->input % 64 == 0 && p->hidden % 64 == 0;
+  if (p->dtype == AMBPTT_BF16 && (any_wide || whole) && wide_pays(p) &&
       (L.mlp ? mlp_wide_fits(p->batch, p->hidden) : cell_wide_fits(L.G, p->batch, p->input, p->hidden))) {
     L.wide = true;
     const int tiles = L.mlp ? mlp_wide_tiles(p->batch, p->hidden) : cell_wide_tiles(L.G, p->batch, p->hidden);
@@ -289,9 +292,11 @@ Layout make_layout(const ambptt_problem* p, int window, bool small_wide = true) 
     o += size_t(L.zc_slots) * L.zc_bytes;
   }
   L.total = o;
-  // a small batch whose workspace fits the scratch array only without the
-  // wide kernels' copies of the weights keeps to the small kernels
-  if (L.wide && p->batch < 48 && L.total > kScratchBytes) {
+  // A small batch, or a width that is an odd multiple of 32, whose workspace
+  // fits the scratch array only without the wide kernels' copies of the
+  // weights and their h-adjoint keeps to the small kernels: ambptt_run_noalloc
+  // takes it.  (RNN of 48 x 1888: 54.6 MB, with them 75.3 MB.)
+  if (L.wide && !whole && L.total > kScratchBytes) {
     const Layout S = make_layout(p, window, false);
     if (S.total <= kScratchBytes) return S;
   }

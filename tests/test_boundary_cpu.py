@@ -103,6 +103,21 @@ def test_query_sizes_and_validation(amb):
     assert e.value.status == -4
 
 
+@pytest.mark.parametrize("cell,batch,input,hidden", [
+    ("rnn", 48, 0, 1888),       # a width that is an odd multiple of 32
+    ("lstm", 512, 800, 352),    # ... and the input's
+    ("lstm", 70, 2560, 608),
+    ("rnn", 116, 160, 992),
+    ("resmlp", 509, 0, 6304),
+    ("lstm", 1, 32, 1792),      # one row, many weights
+])
+def test_wide_copies_do_not_outgrow_the_scratch(amb, cell, batch, input, hidden):
+    # ambptt_run_noalloc's scratch array (64 MiB) holds these passes on the
+    # small-batch kernels, so the wide kernels' copies may not push them out
+    ws = amb.query(amb.ProblemSpec(cell, "bf16", "mean_sq_all", batch, input, hidden, 24, 3))[2]
+    assert ws <= 64 << 20, ws
+
+
 def test_stats_struct_layout(amb):
     from paper_1806_01117_amd import _lib
     st = _lib.Stats()
