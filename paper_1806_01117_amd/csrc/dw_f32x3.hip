@@ -101,7 +101,8 @@ struct DwTile {
         }
       } else {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) column(s + boff + 16 * j, xr[0][j], xr[1][j], xr[2][j], xr[3][j]);
+        for (int j = 0; j < 2; ++j)
+          column(s + boff + 16 * j, xr[0][j] * kScale, xr[1][j] * kScale, xr[2][j] * kScale, xr[3][j] * kScale);
       }
     };
 

@@ -2,6 +2,12 @@
 // value in three bf16 parts, and the stage pipeline of the kernels that
 // multiply split operands (gemm_f32x3.hip, dw_f32x3.hip).
 //
+// Range.  Both operands are scaled by 2^32 before they are split (and their
+// products' sums by 2^-64): an fp32 value down to the smallest subnormal then
+// has its parts in bf16's normal range (unscaled, values below about 2^-110
+// would lose bits).  Values of 2^96 and more and sums of 2^64 and more
+// overflow; such tiles are formed again (any_bad).
+//
 // Rounding.  The matrix cores round a bf16 MFMA's sum of products down (not
 // to nearest), a bias that grows with the length of the chain of
 // accumulations: with one chain through the whole reduction db of the
@@ -27,8 +33,8 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 constexpr int kSt = 32;                         // reduction indices per stage
 constexpr int kFrag = 1024;                     // bytes of one plane of a 16-row fragment
 constexpr int kBlk = 3 * kFrag;                 // ... of its three planes
-constexpr float kScale = 4294967296.0f;         // 2^32
-constexpr float kUnscale = 1.0f / 4294967296.0f;
+constexpr float kScale = 4294967296.0f;         // 2^32, of either operand
+constexpr float kUnscale = 1.0f / 18446744073709551616.0f;  // 2^-64, of their products
 
 __device__ __forceinline__ unsigned pk_bf16(float a, float b) {
   const f2 v = {a, b};

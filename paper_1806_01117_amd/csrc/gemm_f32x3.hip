@@ -15,9 +15,8 @@
 // Infinities, NaNs and sums past fp32's range do not split (inf - inf): every
 // wave looks at its finished accumulators and, if one is not finite, forms
 // its block again with fp32 MFMAs straight from global memory, so such inputs
-// give what the fp32 kernels give.  zbar is scaled by 2^32 before it is split
-// (and the product by 2^-32), so that gradients down to fp32's smallest
-// normal value keep all three parts in bf16's range.
+// give what the fp32 kernels give.  Operands are scaled before they are split
+// (f32x3.hpp), so that the split is exact down to fp32's subnormals.
 //
 // Data flow.  B (the weights, fixed for a pass) is split once per pass into
 // fragment order: the 1 KiB that a wave's MFMA operand needs (16 rows x 32
@@ -80,7 +79,7 @@ struct Tile {
   // past the end of a row meets zeros of B.  Stages st0 .. st1 - 1; len: the
   // most stages that any group of the workgroup has (their barriers are
   // common).  lds: the group's buffers.
-  template <bool TWO, bool SCALE, class BBlk>
+  template <bool TWO, class BBlk>
   static __device__ __forceinline__ void run(const float* x, const float* h, int M, int D, int H, int m0,
                                              const char* Bp, unsigned bbytes, int kb, int st0, int st1, int len,
                                              BBlk bblk, char* lds, f4 (&acc)[MI][NI]) {
@@ -133,9 +132,7 @@ struct Tile {
     auto put = [&](int buf, int p) {
       char* s = lds + buf * STAGE;
       if (p < PA) {
-        f4 v = ra[p];
-        if (SCALE) v *= buf ? -kScale : kScale;
-        else if (buf) v = -v;
+        const f4 v = ra[p] * (buf ? -kScale : kScale);
         u2v p0, p1, p2;
         unsigned t0, t1, t2;
         split2(v.x, v.y, t0, t1, t2);
@@ -154,12 +151,10 @@ struct Tile {
     const int ard = (wm * MI) * kBlk + (16 * q + (r ^ swz(q))) * 16;
     const int brd = ABYTES + (wn * NI) * kBlk + lane * 16;
     x3_pipeline<MI, NI, PA + 1, STAGE, kBlk>(lds, ard, brd, st0, st0 + len, gload, put, acc);
-    if (SCALE) {
 #pragma unroll
-      for (int i = 0; i < MI; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NI; ++j) acc[i][j] *= kUnscale;
-    }
+      for (int j = 0; j < NI; ++j) acc[i][j] *= kUnscale;
   }
 
   // The same sums by fp32 MFMAs from global memory; bval(j, k) is B of the
@@ -342,7 +337,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void cell_f32x3(StepArgs a) {
     for (int j = 0; j < T::NI; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
   const int kb = stages(D) + stages(H);
   const int st0 = kg * kb / KG, st1 = (kg + 1) * kb / KG, len = (kb + KG - 1) / KG;
-  T::template run<true, false>((const float*)a.x, (const float*)a.h, B, D, H, m0, (const char*)a.Wx3,
+  T::template run<true>((const float*)a.x, (const float*)a.h, B, D, H, m0, (const char*)a.Wx3,
                                unsigned(GH / 16) * unsigned(kb) * unsigned(kBlk), kb, st0, st1, len, bblk,
                                lds + kg * 2 * T::STAGE, acc);
   if (KG > 1) __syncthreads();  // every group has left its buffers
@@ -416,7 +411,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG) void prod_f32x3(ProdArgs a, int 
   for (int i = 0; i < T::MI; ++i)
 #pragma unroll
     for (int j = 0; j < T::NI; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-  T::template run<false, true>((const float*)a.A, (const float*)a.A, M, 0, K, m0, (const char*)a.B,
+  T::template run<false>((const float*)a.A, (const float*)a.A, M, 0, K, m0, (const char*)a.B,
                                unsigned(N / 16) * unsigned(kb) * unsigned(kBlk), kb, st0, st1, len, bblk,
                                lds + kg * 2 * T::STAGE, acc);
   if (any_bad(acc)) {
@@ -469,7 +464,7 @@ __global__ void sum_parts_f32(const float* __restrict__ p, int parts, size_t n4,
   ((f4*)out)[i] = s;
 }
 
-// dst <- the planes of src's N rows of K values in fragment order, K padded
+// dst <- the planes of src's N rows of K values (scaled) in fragment order, K padded
 // with zeros to whole stages: steps kb0 .. of the kb steps of a block row.  A
 // thread makes one lane's 16 bytes of the three planes.  TR: src(n, k) =
 // src[k ld + n] (the columns of W_h).
@@ -484,7 +479,7 @@ __global__ __launch_bounds__(256) void pack_f32x3(const float* __restrict__ src,
   float v[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e)
-    v[e] = k < K ? src[TR ? (size_t)(k + e) * ld + n : (size_t)n * ld + k + e] : 0.f;  // K is a multiple of 8
+    v[e] = k < K ? src[TR ? (size_t)(k + e) * ld + n : (size_t)n * ld + k + e] * kScale : 0.f;  // K is a multiple of 8
   u4v p0, p1, p2;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {

@@ -83,6 +83,34 @@ def test_tiny_gradients():
     assert rel_err(a["dh0"], want["dh0"]) <= 1e-5
 
 
+def test_small_operands():
+    # operands near the smallest normal value keep all their bits: inputs,
+    # states and weights of about 1e-37 beside ordinary ones, each in gradients
+    # that they alone make.  (Unscaled, their second and third bf16 parts leave
+    # bf16's range: 1e-4 and more.)  Bound: 2^-24 per rounding, sums of up to
+    # 2048 terms in some 70 roundings, against the largest of the region.
+    B, D, H = 1024, 32, 256
+    wl = synth.get("lstm_h4096_t20000").with_(cell="rnn", loss="half_sq_last", batch=B, input=D, hidden=H, n_steps=2,
+                                              w_scale=H ** -0.5, h0_std=0.3, name="rnn_f32x3_small")
+    x, W, b, x0 = inputs(wl)
+    x, W, x0 = x.copy(), W.copy(), {k: v.copy() for k, v in x0.items()}
+    b = np.zeros_like(b)
+    x[:, :, 16:] *= 1e-37       # dW's columns 16 .. 31
+    W[128:, :] *= 1e-37         # units 128 .. 255: states of that size
+    x0["h"][:, 128:] *= 1e-37   # dW's columns D + 128 ..
+    W[:, D + 64:D + 128] *= 1e-37  # dL/dh_0's columns 64 .. 127
+    dev = device_inputs(wl, x, W, b, x0)
+    want = run_oracle(wl, x, W, b, x0)
+    a = run_gpu(wl, dev, fast_slots=2, slow_slots=0)
+    assert a["stats"]["kernel_calls"][3] == 1  # the large-batch path
+    for k, rows, cols in (("dW", slice(0, 128), slice(16, 32)), ("dW", slice(0, 128), slice(D + 128, D + 256)),
+                          ("dh0", slice(0, B), slice(64, 128))):
+        g, w = np.asarray(a[k], np.float64)[rows, cols], np.asarray(want[k], np.float64)[rows, cols]
+        e = float(np.max(np.abs(g - w)) / np.max(np.abs(w)))
+        say(k, cols, f"largest {np.max(np.abs(w)):.1e}, error {e:.1e}")
+        assert 1e-39 < np.max(np.abs(w)) < 1e-33 and e <= 5e-6, (k, cols)
+
+
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan, 3e38])
 def test_values_that_do_not_split(value):
     # an infinite, NaN or huge input behaves as with the fp32 MFMA kernels
