@@ -109,11 +109,12 @@ struct Tile {
 
     // piece p of stage st to registers: float4 p of A, or (p = PA) the B
     // planes; of a stage past the last, its A again and zeros for B (the
-    // stages go in pairs)
+    // stages go in pairs; of two groups and one stage the first has none, and
+    // takes stage 0's A)
     f4 ra[PA];
     u4v rb[PB];
     auto gload = [&](int st_, int p) {
-      const int st = min(st_, st1 - 1);
+      const int st = max(0, min(st_, st1 - 1));
       if (p < PA) {
         // selects, not a branch: the stage stays one block for the scheduler
         const bool inx = TWO && st < kx;

@@ -47,6 +47,22 @@ def test_against_oracle(cell, B, D, H, n):
             assert e <= 1.5 * e0 + 1e-7, k
 
 
+@pytest.mark.parametrize("B,D,H", [
+    (8192, 0, 32),    # one stage for two wave groups: the first has none
+    (16384, 0, 16),   # ... half of it padding
+    (16390, 16, 16),  # a group for the input's, one for the state's; a last row tile of 6 rows
+])
+def test_shortest_reductions(B, D, H):
+    wl = synth.get("lstm_h4096_t20000").with_(cell="rnn", loss="mean_sq_all", batch=B, input=D, hidden=H, n_steps=3,
+                                              w_scale=H ** -0.5, h0_std=0.3, name="rnn_f32x3_short")
+    host = inputs(wl)
+    dev = device_inputs(wl, *host)
+    a = run_gpu(wl, dev, fast_slots=3, slow_slots=0)
+    assert a["stats"]["kernel_calls"][3] == 2  # the large-batch path
+    assert_close(a, run_oracle(wl, *host), TOL_F32)
+    assert_bitwise(a, run_gpu(wl, dev, fast_slots=2, slow_slots=0))
+
+
 @pytest.mark.parametrize("cell,B,D,H,n,window", [
     ("rnn", 1, 16, 16, 5, 2),       # one row per step, one 16-column block
     ("rnn", 3, 0, 48, 40, 16),      # no input; windows of 48 rows, the last one short
