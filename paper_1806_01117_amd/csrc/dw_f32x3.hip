@@ -204,8 +204,13 @@ bool dw_f32x3_pays(const DwArgs& a) {
 }
 
 bool dw_f32x3_fits(const DwArgs& a) {
+  // Z's offsets are 32-bit, those past its end included: stages go in pairs
+  // and are loaded two ahead (db takes in the first of these two, whose rows
+  // must read zero), and a tile's columns may end 255 past GH
+  const long long stages = (a.R + kSt - 1ll) / kSt;
+  const unsigned long long rows = (stages + stages % 2 + 2ull) * kSt;
   return a.R >= 1 && a.GH >= 16 && a.GH % 16 == 0 && a.D % 16 == 0 && a.H % 16 == 0 &&
-         4ull * (a.R + 2 * kSt) * a.GH < (1ull << 32);
+         4ull * (rows * a.GH + 256) < (1ull << 32);
 }
 
 hipError_t launch_dw_f32x3(const DwArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {

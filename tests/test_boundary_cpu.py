@@ -118,6 +118,29 @@ def test_wide_copies_do_not_outgrow_the_scratch(amb, cell, batch, input, hidden)
     assert ws <= 64 << 20, ws
 
 
+class _DwArgs(ctypes.Structure):
+    _fields_ = [(k, ctypes.c_void_p) for k in ("zbar", "x", "hwin", "dW", "db")] + \
+               [(k, ctypes.c_int) for k in ("R", "D", "H", "GH", "accumulate")]
+
+
+@pytest.mark.parametrize("GH", [16, 48, 4096, 16384])
+def test_split_weight_gradient_offsets_stay_below_4_gib(amb, GH):
+    # the kernel's 32-row stages go in pairs and are loaded two ahead: the
+    # offsets of the rows past the last one must not wrap to the first ones
+    fits = ctypes.CDLL(amb.LIB_PATH)["_ZN6ambptt13dw_f32x3_fitsERKNS_6DwArgsE"]
+    fits.restype, fits.argtypes = ctypes.c_bool, [ctypes.POINTER(_DwArgs)]
+    edge = 2 ** 30 // GH  # rows whose 4-byte values fill 4 GiB
+    taken = 0
+    for R in range(max(1, edge - 512), edge + 1):
+        if not fits(_DwArgs(R=R, D=0, H=16, GH=GH)):
+            continue
+        taken += 1
+        stages = -(-R // 32)
+        last = (2 * -(-stages // 2) + 2) * 32 - 1  # the last row that is loaded
+        assert 4 * (last * GH + -(-GH // 256) * 256) <= 2 ** 32, R
+    assert taken > 300  # the kernel is refused near the edge only
+
+
 def test_stats_struct_layout(amb):
     from paper_1806_01117_amd import _lib
     st = _lib.Stats()
