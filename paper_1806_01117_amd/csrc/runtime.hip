@@ -2124,7 +2124,7 @@ static ambptt_status run_pass(ambptt_ctx* C, const void* x_seq, const void* W, c
   if ((s = E.grow_slots(plan.slot_ids)) != AMBPTT_OK) return s;
   std::fill(C->pend.begin(), C->pend.end(), kNone);
   const size_t GH = (size_t)L.G * p.hidden;
-  if (!L.mlp) {  // windows accumulate into dW; the MLP writes each layer once
+  if (!L.mlp && !L.mlpv) {  // windows accumulate into dW; the MLPs write each layer's once
     HIPCK(launch_fill32(dW, GH * (p.input + p.hidden), 0u, C->cs));
     HIPCK(launch_fill32(db, GH, 0u, C->cs));
   }

@@ -78,6 +78,27 @@ def test_mlp_of_different_widths(shape):
     assert_bitwise(dyn, ref)
 
 
+@pytest.mark.parametrize("n,widths", [(1, (128, 64)), (2, (128, 16)), (1, (16, 128))])
+def test_a_short_mlp_writes_its_gradients_and_nothing_else(n, widths):
+    # few narrow layers: the parameters are fewer than hidden x hidden
+    import torch
+
+    import paper_1806_01117_amd as amb
+    wl = synth.get("mlp_widths_l2000").with_(n_steps=n, batch=20, hidden=128, widths=widths)
+    (x, W, b, x0), dev = _case(wl)
+    want = run_oracle(wl, x, W, b, x0)
+    guard = torch.full((W.size + 2 * 128 * 128,), -7.0, device="cuda"), torch.full((b.size + 512,), -7.0, device="cuda")
+    out = {"dW": guard[0][:W.size], "db": guard[1][:b.size], "dh0": torch.empty((20, widths[0]), device="cuda")}
+    r = amb.Runner(amb.ProblemSpec.from_workload(wl, fast_slots=n, slow_slots=0))
+    try:
+        got = r.run(*dev, out=out)
+    finally:
+        r.close()
+    assert bool((guard[0][W.size:] == -7.0).all()) and bool((guard[1][b.size:] == -7.0).all())
+    assert_close_mlp({k: v.cpu().numpy() if hasattr(v, "cpu") else v for k, v in got.items() if v is not None}, want,
+                     wl, TOL_F32)
+
+
 def test_mlp_widths_refusals():
     import paper_1806_01117_amd as amb
     from paper_1806_01117_amd._lib import EINVAL, EUNSUPPORTED, AmbpttError
