@@ -317,11 +317,12 @@ ambptt_status ambptt_bind(ambptt_ctx* ctx, void* slot_pool, size_t pool_bytes,
  * only when nothing else occupies it, else the pass ends in the barrier
  * timeout), "resident_test_stall" (1: the resident program starts with a wait
  * that is never satisfied, so the pass ends in that timeout; for tests of the
- * abort path), "wide_batch" (1, default: batches of 48 rows and more in bf16,
- * and smaller ones with 2 M weights or more (the residual MLP: 1 M per
- * layer), run the wide-batch kernels, but for small batches and odd multiples
- * of 32 whose workspace ambptt_run_noalloc holds only without them; 0: the
- * small-batch kernels), "dw_stream" (1:
+ * abort path), "wide_batch" (1, default: batches of 48 rows and
+ * more in bf16 whose sizes are multiples of 64, residual MLPs of 48 rows or
+ * 1 M weights per layer, and other cells whose steps are large (batch times
+ * weights 100 M for the LSTM, 2^28 for the RNN) run the wide-batch kernels,
+ * but for those of the last two kinds whose workspace ambptt_run_noalloc
+ * holds only without them; 0: the small-batch kernels), "dw_stream" (1:
  * weight-gradient windows run on a stream of their own, beside the steps; 0:
  * on the compute stream, after the window's last adjoint; -1, default: 0 on
  * the wide-batch bf16 path and the large-batch fp32 path, whose kernels each

@@ -150,19 +150,29 @@ int auto_window(const ambptt_problem* p) {
 }
 
 // Whether a bf16 problem of this size takes the wide kernels (where its shape
-// fits them): any batch of 48 rows, and smaller ones whose weights are many.
-// The wide path's adjoint is two launches, its kernels read the weights in
-// whole lines: at 20 x 1024 (D 512, 6.3 M weights) a forward step takes 6.9 us
-// against 8.1 and an adjoint 5.1 + 5.7 against 11-16, at 32 x 2048 (D 512)
-// 10.4 against 20.3 and 5.3 + 7.2 against 33.7; passes at 8 x 512 (D 128, 1.3 M)
-// are equal, at 32 x 1024 (tanh RNN, 1.2 M) 6 % slower.  The residual MLP's
-// kept adjoint is one launch on both: 20 x 1024 (1 M) 16 % faster, 40 x 4096
-// 33 %.
-bool wide_pays(const ambptt_problem* p) {
-  if (p->batch >= 48) return true;
-  const double H = p->hidden, weights = p->cell == AMBPTT_CELL_RESMLP ? 2.0 * H * H
-                                        : (p->cell == AMBPTT_CELL_LSTM ? 4.0 : 1.0) * H * (double(p->input) + H);
-  return weights >= double(1 << 21);
+// fits them): 48 rows and more in whole 64-wide blocks always, the residual
+// MLP also at any 32-wide blocks or from 1 M weights per layer (its kept
+// adjoint is one launch: 48 x 160 456 us for 24 layers against 756, 20 x 1024
+// 584 against 711).  The other cells pay for the wide path's two launches per
+// adjoint, which the small-batch kernels do in one: only steps of many
+// products win (24 steps on 6 slots, wide / small kernels, LSTM: 20 x (512 +
+// 1024), 126 M, equal; 32 x (480 + 736), 115 M, 538 / 588 us; 64 x (96 + 608),
+// 109 M, 564 / 643; 256 x (160 + 992) 1116 / 2172; 47 x (96 + 608), 80 M,
+// equal; but 512 x (96 + 288), 0.4 M weights, 1167 / 1090.  tanh RNN: 256 x
+// (160 + 992), 292 M, 745 / 863; 64 x (512 + 1504), 194 M, 647 / 635; 48 x (96 +
+// 608) 496 / 396, 512 x (480 + 608), 0.7 M weights, 1065 / 976, 32 x (1024 +
+// 4096) 1000 / 914).  At an interval of one nothing is kept and a wide pass
+// is up to 7 % slower near these lines.
+bool wide_pays(const ambptt_problem* p, bool whole) {
+  const double B = p->batch, H = p->hidden, D = p->input;
+  if (whole) return true;
+  if (p->cell == AMBPTT_CELL_RESMLP) return p->batch >= 48 || 2.0 * H * H >= double(1 << 21);
+  if (p->cell == AMBPTT_CELL_LSTM) {
+    const double weights = 4.0 * H * (D + H);
+    return weights >= double(1 << 19) && B * weights >= 1.0e8;
+  }
+  const double weights = H * (D + H);
+  return p->batch >= 48 && weights >= double(1 << 20) && B * weights >= double(1 << 28);
 }
 
 Layout make_layout(const ambptt_problem* p, int window, bool any_wide = true) {
@@ -198,7 +208,7 @@ Layout make_layout(const ambptt_problem* p, int window, bool any_wide = true) {
   // 48 rows and more in whole 64-wide blocks take the wide kernels whatever
   // their workspace; the others only if it costs them no call (below)
   const bool whole = p->batch >= 48 && p->input % 64 == 0 && p->hidden % 64 == 0;
-  if (p->dtype == AMBPTT_BF16 && (any_wide || whole) && wide_pays(p) &&
+  if (p->dtype == AMBPTT_BF16 && (any_wide || whole) && wide_pays(p, whole) &&
       (L.mlp ? mlp_wide_fits(p->batch, p->hidden) : cell_wide_fits(L.G, p->batch, p->input, p->hidden))) {
     L.wide = true;
     const int tiles = L.mlp ? mlp_wide_tiles(p->batch, p->hidden) : cell_wide_tiles(L.G, p->batch, p->hidden);
