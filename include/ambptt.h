@@ -304,9 +304,18 @@ ambptt_status ambptt_create(const ambptt_problem* p, void* stream, ambptt_ctx** 
 ambptt_status ambptt_bind(ambptt_ctx* ctx, void* slot_pool, size_t pool_bytes,
                           void* workspace, size_t workspace_bytes);
 
+/* The workspace bytes that ambptt_bind wants with the context's settings:
+ * what ambptt_query reports, or less after "kept_steps".  0 for NULL. */
+size_t ambptt_workspace_bytes(const ambptt_ctx* ctx);
+
 /* Sets a tuning / debug knob.  Keys: "timing_sample" (time every k-th
  * kernel launch with events, 0 = off), "elide_prefetch" (0/1, default 1),
- * "window" (dW window steps, 0 = automatic), "path" (0 = the resident
+ * "window" (dW window steps, 0 = automatic), "kept_steps" (0 .. 16, default 16:
+ * how many steps' pre-activations the workspace holds for adjoints that
+ * follow, each 4 B G H bytes in a multiple of 256 and all of them at most
+ * 512 MiB; fewer places make a smaller workspace, see ambptt_workspace_bytes,
+ * and more adjoints form their gate product again, with the same results;
+ * EINVAL if the bound workspace is too small), "path" (0 = the resident
  * whole-pass kernel when the problem and device allow it, else one launch
  * per step; 1 = one launch per step; 2 = resident, EUNSUPPORTED at run time
  * if it does not fit), "resident_timeout_ms" (how long one barrier wait of the

@@ -16,7 +16,7 @@ EXPORTS = ["ambptt_version", "ambptt_revolve_advances", "ambptt_schedule_evals",
            "ambptt_schedule_text_starts", "ambptt_schedule_text_starts_costs", "ambptt_schedule_text_online", "ambptt_schedule_text_costs", "ambptt_schedule_text_sized",
            "ambptt_interval_from_timings", "ambptt_set_step_costs", "ambptt_set_widths",
            "ambptt_resident_program", "ambptt_query", "ambptt_last_error",
-           "ambptt_create", "ambptt_bind", "ambptt_set_int", "ambptt_set_file_tier", "ambptt_calibrate", "ambptt_run", "ambptt_run_noalloc",
+           "ambptt_create", "ambptt_bind", "ambptt_workspace_bytes", "ambptt_set_int", "ambptt_set_file_tier", "ambptt_calibrate", "ambptt_run", "ambptt_run_noalloc",
            "ambptt_last_schedule_text", "ambptt_destroy"]
 
 
@@ -106,6 +106,8 @@ def load():
     L.ambptt_create.restype = C.c_int
     L.ambptt_bind.argtypes = [vp, vp, sz, vp, sz]
     L.ambptt_bind.restype = C.c_int
+    L.ambptt_workspace_bytes.argtypes = [vp]
+    L.ambptt_workspace_bytes.restype = sz
     L.ambptt_set_int.argtypes = [vp, C.c_char_p, i64]
     L.ambptt_set_int.restype = C.c_int
     L.ambptt_calibrate.argtypes = [vp, vp, vp, vp, vp, vp, C.POINTER(i32), C.POINTER(C.c_double),

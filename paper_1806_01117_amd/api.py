@@ -219,7 +219,20 @@ class Runner:
         return x, W, b, h0, (c0 if s.cell == "lstm" else None)
 
     def set(self, key: str, value: int) -> None:
-        check(self.L.ambptt_set_int(self.ctx, key.encode(), int(value)))
+        if key != "kept_steps":
+            check(self.L.ambptt_set_int(self.ctx, key.encode(), int(value)))
+            return
+        # the workspace shrinks or grows with it
+        check(self.L.ambptt_bind(self.ctx, _ptr(self.pool), self.pool.numel(), None, 0))
+        try:
+            check(self.L.ambptt_set_int(self.ctx, b"kept_steps", int(value)))
+            need = max(self.L.ambptt_workspace_bytes(self.ctx), 256)
+            if need != self.ws.numel():
+                self.ws = None  # the old one goes first
+                self.ws = self.torch.empty(need, dtype=self.torch.uint8, device=self.device)
+        finally:
+            n = self.ws.numel() if self.ws is not None else 0
+            check(self.L.ambptt_bind(self.ctx, _ptr(self.pool), self.pool.numel(), _ptr(self.ws), n))
 
     def calibrate(self, x, W, b, h0, c0=None) -> tuple[int, float, float]:
         x, W, b, h0, c0 = self._inputs(x, W, b, h0, c0)

@@ -69,8 +69,8 @@ struct Layout {
   // large-batch fp32 cell on the bf16 matrix cores: W's and W_h^T's split planes
   bool x3 = false;
   size_t off_wx3 = 0, off_whx3 = 0;
-  // ring of zc_slots steps' pre-activations (fp32): a forward step whose
-  // adjoint comes next leaves them for it
+  // ring of zc_slots steps' pre-activations (fp32), the last part of the
+  // workspace: a forward step whose adjoint comes next leaves them for it
   int zc_slots = 0;
   size_t off_zc = 0, zc_bytes = 0;
   int ld_wht = 0;        // row stride of WhT in elements
@@ -103,6 +103,9 @@ static __device__ __align__(256) char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 char* g_scratch[kMaxDevices] = {};
+
+// Places of the ring of kept pre-activations.
+constexpr int kKeptSteps = 16;
 
 // Largest grid of the resident kernel the layout provisions for; the device's
 // own limit is checked when a context is created.
@@ -297,7 +300,7 @@ Layout make_layout(const ambptt_problem* p, int window, bool any_wide = true) {
     L.zc_bytes = align_up(BH * size_t(L.G) * 4);
     size_t room = size_t(512) << 20;
     if (o <= kScratchBytes) room = std::min(room, kScratchBytes - o);
-    L.zc_slots = int(std::min<size_t>({size_t(16), size_t(p->n_steps), room / L.zc_bytes}));
+    L.zc_slots = int(std::min<size_t>({size_t(kKeptSteps), size_t(p->n_steps), room / L.zc_bytes}));
     L.off_zc = o;
     o += size_t(L.zc_slots) * L.zc_bytes;
   }
@@ -327,6 +330,7 @@ struct ambptt_ctx {
   std::vector<hipEvent_t> tpool;  // timing events, reused across runs
   char* pool = nullptr;
   char* ws = nullptr;
+  size_t ws_bytes = 0;
   // Pinned host tier: chunks of host_per_chunk slots of host_slot_bytes each
   // (one pinned allocation of tens of GiB fails well below the per-process
   // pinned limit, so a large tier comes in chunks); host is the first chunk,
@@ -1829,8 +1833,11 @@ ambptt_status ambptt_bind(ambptt_ctx* C, void* slot_pool, size_t pool_bytes, voi
   if (workspace && ws_bytes < C->L.total) return fail(AMBPTT_EINVAL, "workspace too small");
   C->pool = (char*)slot_pool;
   C->ws = (char*)workspace;
+  C->ws_bytes = ws_bytes;
   return AMBPTT_OK;
 }
+
+size_t ambptt_workspace_bytes(const ambptt_ctx* C) { return C ? C->L.total : 0; }
 
 static ambptt_status reserve(ambptt_ctx* C);
 
@@ -1849,6 +1856,14 @@ ambptt_status ambptt_set_int(ambptt_ctx* C, const char* key, int64_t v) {
     const Layout L2 = make_layout(&C->p, int(v == 0 ? wmax : v));
     // same offsets except the rings, which only shrink
     C->L.window = L2.window;
+  } else if (k == "kept_steps") {
+    if (v < 0 || v > kKeptSteps) return fail(AMBPTT_EINVAL, "kept_steps must be 0 .. " + std::to_string(kKeptSteps));
+    const Layout D = make_layout(&C->p, 0);  // the ring ends the workspace: only its places change
+    const int slots = std::min(D.zc_slots, int(v));
+    const size_t total = D.total - size_t(D.zc_slots - slots) * D.zc_bytes;
+    if (C->ws && C->ws_bytes < total) return fail(AMBPTT_EINVAL, "kept_steps: the bound workspace is too small");
+    C->L.zc_slots = slots;
+    C->L.total = total;
   } else if (k == "path") {
     if (v < 0 || v > 2) return fail(AMBPTT_EINVAL, "path must be 0 (auto), 1 (per-step launches) or 2 (resident)");
     C->path_opt = int(v);

@@ -36,3 +36,40 @@ def test_kept_equals_formed_again(base, kw, opts):
         if wl.cell == "mlp" and slots == N:
             slots = 12  # its sized schedule's table grows with the slots
         assert_bitwise(again, run_gpu(wl, dev, path=path, fast_slots=slots, slow_slots=host, interval_min=interval))
+
+
+@pytest.mark.parametrize("base,kw", [
+    ("lstm_h512_t1000", dict(batch=20, input=16, hidden=1040)),                                 # step_small
+    ("lstm_h2048_bf16_t10000", dict(batch=70, input=64, hidden=128, loss="mean_sq_all")),       # wide bf16
+    ("lstm_h4096_t20000", dict(batch=260, input=16, hidden=1040, w_scale=1.0 / 32, loss="mean_sq_all")),  # split fp32
+    ("resmlp_w4096_l2000_bf16", dict(batch=70, hidden=128, w_scale=0.05, loss="mean_sq_all")),  # wide residual MLP
+])
+def test_fewer_places(base, kw):
+    # the ring of kept steps may be smaller or absent: the workspace shrinks by
+    # its places and the results stay
+    import paper_1806_01117_amd as amb
+    from paper_1806_01117_amd._lib import EINVAL, AmbpttError
+    wl = synth.get(base).with_(n_steps=N, name=base + "_places", **kw)
+    dev = device_inputs(wl, *inputs(wl))
+    want = run_gpu(wl, dev, fast_slots=4, slow_slots=N, interval_min=20)
+    place = -(-4 * wl.batch * wl.gates * wl.hidden // 256) * 256
+    r = amb.Runner(amb.ProblemSpec.from_workload(wl, fast_slots=4, slow_slots=N, interval_min=20))
+    full = r.ws.numel()
+    assert r.L.ambptt_workspace_bytes(r.ctx) == full
+    try:
+        for kept in (5, 0, 1, 16):
+            r.set("kept_steps", kept)
+            assert r.ws.numel() == full - (16 - kept) * place
+            got = r.run(*dev)
+            assert_bitwise(want, {k: (v.cpu().numpy() if hasattr(v, "cpu") else v) for k, v in got.items() if v is not None})
+        with pytest.raises(AmbpttError) as e:
+            r.set("kept_steps", 17)
+        assert e.value.status == EINVAL
+        r.set("kept_steps", 3)
+        with pytest.raises(AmbpttError) as e:  # the workspace that is bound has three places
+            from paper_1806_01117_amd._lib import check
+            check(r.L.ambptt_set_int(r.ctx, b"kept_steps", 4))
+        assert e.value.status == EINVAL
+        r.run(*dev)
+    finally:
+        r.close()
