@@ -28,6 +28,7 @@ def _rms(got, want):
     ("lstm", 1030, 32, 1248, 3),   # 256-row tiles, the last of 6 rows
     ("rnn", 300, 0, 1040, 6),      # no input; one gate
     ("rnn", 1100, 80, 272, 6),     # K below two stages per part
+    ("rnn", 4100, 16, 1104, 3),    # 256-row tiles with one gate, the last of 4 rows, units past the last tile
 ])
 def test_against_oracle(cell, B, D, H, n):
     wl = synth.get("lstm_h4096_t20000").with_(cell=cell, loss="mean_sq_all", batch=B, input=D, hidden=H, n_steps=n,
@@ -40,6 +41,7 @@ def test_against_oracle(cell, B, D, H, n):
     assert_bitwise(a, run_gpu(wl, dev, fast_slots=n, slow_slots=0))   # store-all
     assert_bitwise(a, run_gpu(wl, dev, fast_slots=2, slow_slots=0))   # plain Revolve
     old = run_gpu(wl, dev, fast_slots=3, slow_slots=n, interval_min=2, opts={"lds_gemm": 2})
+    assert not np.array_equal(a["dh0"], old["dh0"])  # other kernels
     for k in KEYS:
         if k in want and k != "loss":
             e, e0 = _rms(a[k], want[k]), _rms(old[k], want[k])
@@ -64,9 +66,11 @@ def test_shortest_reductions(B, D, H):
 
 
 @pytest.mark.parametrize("cell,B,D,H,n,window", [
-    ("rnn", 1, 16, 16, 5, 2),       # one row per step, one 16-column block
-    ("rnn", 3, 0, 48, 40, 16),      # no input; windows of 48 rows, the last one short
-    ("lstm", 20, 48, 80, 33, 8),    # columns past the last tile of both operands
+    ("lstm", 1, 176, 80, 5, 1),     # windows of one row
+    ("lstm", 20, 176, 80, 9, 1),    # ... of 20: less than a stage
+    ("rnn", 3, 0, 48, 70, 24),      # no input; windows of 72 and 66 rows (three stages: a padded fourth)
+    ("rnn", 3, 0, 48, 70, 40),      # ... of 120 and 90 rows (four stages, and three)
+    ("lstm", 20, 48, 80, 32, 8),    # columns past the last tile of both operands
     ("lstm", 33, 144, 128, 9, 31),  # the input ends inside a column tile; one window of 297 rows
 ])
 def test_weight_gradient_windows(cell, B, D, H, n, window):
@@ -80,6 +84,7 @@ def test_weight_gradient_windows(cell, B, D, H, n, window):
     assert_close(a, want, TOL_F32)
     assert_bitwise(a, run_gpu(wl, dev, path=1, window=window, fast_slots=n, slow_slots=0))
     old = run_gpu(wl, dev, path=1, window=window, fast_slots=3, slow_slots=n, interval_min=2, opts={"lds_gemm": 2})
+    assert not np.array_equal(a["dW"], old["dW"])  # two kernels, so two orders of summation
     for k in ("dW", "db"):
         e, e0 = _rms(a[k], want[k]), _rms(old[k], want[k])
         say(k, f"{e:.2e} split, {e0:.2e} fp32 MFMA")

@@ -43,7 +43,11 @@ def test_cells(cell, B, D, H, n, wide):
     assert_bitwise(a, run_gpu(wl, dev, fast_slots=2, slow_slots=0))
 
 
-@pytest.mark.parametrize("B,w,n", [(70, 160, 9), (200, 1056, 4), (7, 1056, 5)])
+@pytest.mark.parametrize("B,w,n", [
+    (70, 160, 9), (200, 1056, 4), (7, 1056, 5),  # 16-row tiles
+    (250, 1312, 4),                              # 32-row tiles, the last of 26 rows
+    (250, 2592, 3),                              # 64-row tiles, the last of 58 rows
+])
 def test_residual_mlp(B, w, n):
     wl = synth.get("resmlp_w4096_l2000_bf16").with_(batch=B, hidden=w, n_steps=n, w_scale=0.9 / w ** 0.5,
                                                     name="resmlp_wide_ragged")
