@@ -265,7 +265,7 @@ Layout make_layout(const ambptt_problem* p, int window, bool any_wide = true) {
   L.off_loss = o; o += align_up((size_t)L.loss_slots * 8);
   L.off_lossout = o; o += kAlign;
   L.hsep = !L.small && !L.mlp && !L.mlpv && p->dtype == AMBPTT_F32;
-  if (L.wide || L.hsep || L.mlpv) {  // the fp32 large-batch path may hold the product in split parts
+  if (L.wide || L.hsep) {  // the fp32 large-batch path may hold the product in split parts
     L.off_hbar = o; o += align_up(BH * 4 * (L.hsep ? kProdSplitMax : 1));
   }
   if (L.res) {
@@ -678,7 +678,7 @@ struct Exec {
       // the split parts are summed by the LDS-tiled adjoint only
       if (lds_prod && lds_cell && C->prod_split) hparts = prod_split_f32_parts(B, H, G * H);
     }
-    if (wide || sep32 || L.mlpv) hbuf = (float*)(C->ws + L.off_hbar);
+    if (wide || sep32) hbuf = (float*)(C->ws + L.off_hbar);
     if (wide && !L.mlp) {
       Wpk = C->ws + L.off_wpk;
       WhPk = C->ws + L.off_whpk;
