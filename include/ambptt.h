@@ -359,15 +359,17 @@ size_t ambptt_workspace_bytes(const ambptt_ctx* ctx);
  * gradients), "uniform_sizes" (states of different sizes: 1 plans the
  * schedule as if every state had the size of the largest, i.e. slots of the
  * largest size in the same byte budget, for comparison with the sized
- * schedule; 0 by default), "lds_gemm" (fp32 path for large batches: 1, default, runs the gate
- * product with its cell epilogue and the h-adjoint product on the bf16 matrix
- * cores, each fp32 operand split exactly into three bf16 parts and the six
- * products that fp32 can tell apart summed in fp32 (with "hadj_launch" and
- * "prod_split" 1; operands under 4 GiB), and so every fp32 cell's
- * weight-gradient windows; elsewhere, as with 2 and without the split, on LDS-tiled fp32 MFMA kernels
- * (128 x 128 and 64 x 64 tiles, two workgroups per CU) where they
- * have at least 256 tiles; 2 wherever their shape constraints hold; 0 never:
- * the direct-load kernels), "hadj_launch" (1,
+ * schedule; 0 by default), "lds_gemm" (fp32 path for large batches: 1,
+ * default, runs the gate product with its cell epilogue and the h-adjoint
+ * product on the bf16 matrix cores, each fp32 operand split exactly into
+ * three bf16 parts and six of their nine products summed in fp32 (what is
+ * left out is at most 2^-24 of a product; with "hadj_launch" and "prod_split"
+ * 1; operands under 4 GiB), and so the fp32 weight-gradient windows of more
+ * than 64 rows or of gradients of 256 x 256 and more (not those of the MLP of
+ * layers of different widths); elsewhere, as with 2 and without the split, on
+ * LDS-tiled fp32 MFMA kernels (128 x 128 and 64 x 64 tiles, two workgroups
+ * per CU) where they have at least 256 tiles; 2 wherever their shape
+ * constraints hold; 0 never: the direct-load kernels), "hadj_launch" (1,
  * default: on the fp32 path for large batches the adjoint's h-adjoint
  * product zbar_{t+1} W_h runs as a launch of its own, kernel class
  * AMBPTT_K_HADJ; 0: fused into the adjoint step's launch), "prod_split" (1,

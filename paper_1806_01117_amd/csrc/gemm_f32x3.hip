@@ -4,13 +4,15 @@
 //
 // An fp32 value is the exact sum of three bf16 values, a = a0 + a1 + a2 (each
 // the nearest bf16 to what the ones before it leave: 3 x 8 significant bits
-// and two signs cover fp32's 24).  Of the nine products of two such sums the
-// six down to 2^-18 of the largest are formed, a0 b0 + a0 b1 + a1 b0 + a1 b1 +
-// a0 b2 + a2 b0; what is left out is below 2^-26 of |a b|, under fp32's own
-// rounding.  Every product of two bf16 values is exact in the fp32
-// accumulators, so a 32-wide reduction step costs 6
-// v_mfma_f32_16x16x32_bf16 (96 cycles) where v_mfma_f32_16x16x4_f32 takes 8
-// (256 cycles), and it rounds its accumulator 6 times instead of at least 8.
+// and two signs cover fp32's 24).  Of the nine products of two such sums six
+// are formed, a0 b0 + a0 b1 + a1 b0 + a1 b1 + a0 b2 + a2 b0.  With |a1| <=
+// 2^-8 and |a2| <= 2^-17 of a's power of two, a1 b2 + a2 b1, the larger of
+// what is left out, comes to at most 2^-24 of |a b| (2^-26.5 rms over random
+// operands): no more than one rounding to fp32.  Every product of two bf16
+// values is exact in the fp32 accumulators, so a 32-wide reduction step costs
+// 6 v_mfma_f32_16x16x32_bf16 (96 cycles) where v_mfma_f32_16x16x4_f32 takes 8
+// (256 cycles): six MFMAs summed from zero, then one VALU add to the
+// accumulators (f32x3.hpp).
 //
 // Infinities, NaNs and sums past fp32's range do not split (inf - inf): every
 // wave looks at its finished accumulators and, if one is not finite, forms
@@ -25,7 +27,6 @@
 // read as fp32 rows and split on its way to LDS: the split's VALU work hides
 // under the MFMAs, and the operand moves 4 bytes per element from L2 instead
 // of 6.  LDS holds two stages of 32 reduction indices.
-//
 #include <hip/hip_runtime.h>
 
 #include "ambptt.h"

@@ -80,8 +80,8 @@ struct Layout {
   bool small = false;    // one-launch small-batch path (step_small)
   bool mlp = false;      // residual MLP (per-layer weights, one-step dW windows)
   bool mlpv = false;     // MLP of layers of different widths (per-layer weights, states of different sizes)
-  // wide-batch bf16 path (B >= 48): cell / layer kernels over up to 128 rows,
-  // the adjoint's products as launches of their own (wide_bf16.hip)
+  // wide-batch bf16 path (wide_pays): cell / layer kernels, the adjoint's
+  // products as launches of their own (wide_bf16.hip)
   bool wide = false;
   size_t off_hbar = 0;   // fp32 [B][H]: hbar_{t+1} (cell) or ybar_{l+2} + zbar_{l+1} W_{l+1} (MLP)
   bool hsep = false;     // fp32 step kernels of large batches: the h-adjoint product may run as its own launch

@@ -1,5 +1,6 @@
 // Wide-batch bf16 step kernels (gfx950): the LSTM / tanh-RNN cell and the
-// residual MLP when the batch has 48 rows or more.
+// residual MLP for batches of 48 rows and more and for smaller ones whose
+// weights are many.
 //
 // At these shapes a step is a short, fat GEMM (the 2048-wide LSTM: 128 x 8192
 // x 3072 with a 50 MB weight matrix; the 4096-wide MLP layer: 256 x 4096 x
