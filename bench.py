@@ -118,7 +118,7 @@ def mlp_layer_work(ws, B: int) -> tuple[dict, dict]:
     recomputed z_l, the seed and u = z-bar_{l+1} W_{l+1}, formed in the same
     launch (no u for the last layer), with the copy of y_l kept for the
     weight gradient; the weight gradient of one layer.  (The library's adjoint
-    reads its mask and forms u alone; the count is of the layer's own work.)"""
+    launch does less: mlp_adjoint_launch.)"""
     n = len(ws) - 1
     f = {"fwd": 0.0, "adj": 0.0, "dw": 0.0}
     b = dict(f)
@@ -135,6 +135,21 @@ def mlp_layer_work(ws, B: int) -> tuple[dict, dict]:
         f["dw"] += 2.0 * B * c * (a + 1)
         b["dw"] += 4.0 * (B * c + B * a + c * a + c)              # z-bar_l, y_l in; dW_l, db_l written once
     return {k: v / n for k, v in f.items()}, {k: v / n for k, v in b.items()}
+
+
+def mlp_adjoint_launch(ws, B: int) -> tuple[float, float]:
+    """Flops and HBM bytes of one adjoint launch of that MLP as the library
+    runs it, averaged over its layers: the last layer's forms z; the others
+    read their mask from the kept copy of y_{l+1} and form only u."""
+    n = len(ws) - 1
+    a, c = ws[n - 1], ws[n]
+    f = 2.0 * B * a * c
+    b = 4.0 * (c * a + c + B * a + B * c + B * a)                 # W_l, b_l, y_l in; z-bar_l and the copy of y_l out
+    for l in range(n - 1):
+        a, c, d = ws[l], ws[l + 1], ws[l + 2]
+        f += 2.0 * B * c * d
+        b += 4.0 * (B * d + d * c + B * c + B * a + B * c + B * a)  # z-bar_{l+1}, W_{l+1}, y_{l+1}, y_l in; z-bar_l, y_l out
+    return f / n, b / n
 
 
 _HASH_CHUNK = 64 << 20  # 4-byte elements per hashed chunk (256 MiB)
@@ -237,6 +252,25 @@ def split_f32(spec, knobs) -> bool:
     return spec.dtype == "f32" and all(k.get(n, 1) == 1 for n in ("lds_gemm", "hadj_launch", "prod_split"))
 
 
+def split_dw(spec, knobs, window: int) -> bool:
+    """Whether a whole fp32 weight-gradient window runs on the bf16 matrix
+    cores (the library's rule: "lds_gemm" 1, and more than 64 rows or a
+    gradient of 256 x 256 and more; not the MLP of different widths)."""
+    if spec.dtype != "f32" or spec.cell == "mlp" or dict(knobs).get("lds_gemm", 1) != 1:
+        return False
+    return window * spec.batch > 64 or min(spec.gates * spec.hidden, spec.input + spec.hidden) >= 256
+
+
+def keeps_steps(spec, knobs, wide: bool) -> bool:
+    """Whether the path can keep a step's pre-activations for its adjoint: all
+    per-step paths but the MLP of different widths and the fp32 MFMA kernels
+    of large batches."""
+    if spec.cell == "mlp" or dict(knobs).get("kept_steps", 16) == 0:
+        return False
+    large = spec.dtype == "f32" and spec.cell in ("rnn", "lstm") and -(-spec.batch // 16) * (spec.hidden // 16) >= 1024
+    return not large or (wide and split_f32(spec, knobs))
+
+
 def prod_split_parts(spec, knobs) -> int:
     """Parts of the fp32 h-adjoint product's split reduction (the library's
     "prod_split" rule: both LDS-tiled kernels in use, 128 x 128 tiles, parts
@@ -286,6 +320,7 @@ def step_bytes(wl, spec, window: int, wide: bool) -> dict:
         if not wide:
             adj += zbar + W + f                     # the next layer's zbar, W_{l+1} and ybar feed the product
         hadj = zbar + W + 2 * f
+        back = zbar + W + 2 * f + h + f + zbar + h  # ybar, z and y in, ybar, zbar and the y window out
         dw = 2 * B * H * e + W // e * 4 + b         # zbar and y of one layer in, dW_l and db_l written once
     else:
         fwd = W + b + B * K1 * e + c + h + c
@@ -295,7 +330,8 @@ def step_bytes(wl, spec, window: int, wide: bool) -> dict:
         hadj = zbar + GH * H * e + f
         R = window * B
         dw = R * GH * e + R * K1 * e + 2 * (GH * K1 * 4 + b)   # the window's operands, dW and db read and written
-    return {"fwd": fwd, "adj": adj, "hadj": hadj, "dw": dw}
+        back = None
+    return {"fwd": fwd, "adj": adj, "hadj": hadj, "dw": dw, "back": back}
 
 
 def measured_traffic(workload: str, kernel: str):
@@ -730,12 +766,11 @@ def _measure(args, knobs, wl, spec, host_slots, pinned_cap, dev, dx, dW, db, dh,
     from paper_1806_01117_amd._lib import KERNEL_CLASSES
     peak = FP32_MFMA_PEAK_TFLOPS if wl.dtype == "f32" else BF16_MFMA_PEAK_TFLOPS
     wide = st["kernel_calls"][3] > 0
-    # six bf16 products in the place of an fp32 one: the bound is a sixth of the bf16 peak
     split = split_f32(spec, knobs) and wide and wl.cell in ("rnn", "lstm")
-    if split:
-        peak = BF16_MFMA_PEAK_TFLOPS / 6.0
+    dw_x3 = not resident and split_dw(spec, knobs, st["window"])
     if wl.cell == "mlp":
         fl, byts = mlp_layer_work(wl.layer_widths(), wl.batch)
+        fl["adj"], byts["adj"] = mlp_adjoint_launch(wl.layer_widths(), wl.batch)
     else:
         fl = step_flops(spec, st["window"], wide)
         byts = step_bytes(wl, spec, st["window"], wide)
@@ -759,8 +794,19 @@ def _measure(args, knobs, wl, spec, host_slots, pinned_cap, dev, dx, dW, db, dh,
     else:
         flops = {k: fl[k] for k in ("fwd", "adj", "hadj", "dw") if k in fl}
         # an adjoint whose step's pre-activations are kept forms no gate product,
-        # and the class holds both kinds: its launches have no one flop count
-        cand = [k for k in tot if k in flops and k != "adj"]
+        # and the class holds both kinds: its launches have no one flop count.
+        # The wide residual MLP's kept adjoints are product and adjoint in one
+        # launch of the product's class.
+        mixed = {"adj"} if keeps_steps(spec, knobs, wide) else set()
+        back = False
+        if wide and wl.cell == "resmlp":
+            n_adj = st["kernel_calls"][2]  # the first turn's and those that form z again
+            back = n_adj == 1
+            if back:
+                byts["hadj"] = byts["back"]
+            elif n_adj < st["adjoints"]:
+                mixed.add("hadj")
+        cand = [k for k in tot if k in flops and k not in mixed]
         dom = max(cand, key=tot.get) if cand else "adj"
         small = spec.batch * spec.hidden < 1024 * 256 or wl.dtype == "bf16"
         lds_cell, lds_prod = lds_kernels(spec, knobs)
@@ -783,18 +829,24 @@ def _measure(args, knobs, wl, spec, host_slots, pinned_cap, dev, dx, dW, db, dh,
                      "dw": "dw_f32_big weight-gradient window"}
         elif wide and wl.cell == "resmlp":
             names = {"fwd": "mlp_wide forward", "adj": "mlp_wide adjoint (recompute + mask)",
-                     "hadj": "prod_wide NN product ybar + zbar W_{l+1}", "dw": "dw_bf16 weight gradient of one layer"}
+                     "hadj": "mlp_back_wide: NN product and the layer's adjoint on its kept z" if back else
+                     "prod_wide NN product ybar + zbar W_{l+1}", "dw": "dw_bf16 weight gradient of one layer"}
         elif wide:
             names = {"fwd": "cell_wide forward: gate GEMM + cell update",
                      "adj": "cell_wide adjoint: gate recompute + cell adjoint",
                      "hadj": "prod_wide h-adjoint product zbar W_h", "dw": "dw_bf16 weight-gradient window"}
         elif wl.cell == "resmlp":
             names = {"fwd": "resmlp_step forward", "adj": "resmlp_step adjoint (recompute + NN product)",
-                     "dw": "weight gradient of one layer"}
+                     "dw": ("dw_bf16" if wl.dtype == "bf16" else "dw_f32x3" if dw_x3 else "dw_f32_big / dw_lds_f32")
+                     + " weight gradient of one layer"}
         else:
             k = "step_small" if small else "step_f32"
             names = {"fwd": f"{k} forward: gate GEMM + cell update", "adj": f"{k} adjoint: gate recompute + h-adjoint GEMM",
-                     "dw": ("dw_bf16" if wl.dtype == "bf16" else "dw_lds_f32") + " weight-gradient window"}
+                     "dw": ("dw_bf16" if wl.dtype == "bf16" else "dw_f32x3" if dw_x3 else "dw_lds_f32")
+                     + " weight-gradient window"}
+        # six bf16 products in the place of an fp32 one: the bound is a sixth of the bf16 peak
+        if dw_x3 if dom == "dw" else split:
+            peak = BF16_MFMA_PEAK_TFLOPS / 6.0
         if wl.cell == "mlp":
             key = "mlpv_" + dom
         elif split:
@@ -805,11 +857,13 @@ def _measure(args, knobs, wl, spec, host_slots, pinned_cap, dev, dx, dW, db, dh,
                    "hadj": "prod_split_f32" if prod_split_parts(spec, knobs) > 1 else
                    "prod_gemm_f32" if lds_prod else "prod_f32"}.get(dom, "dw_f32_big")
         elif wide:
-            fam = {"fwd": "mlp_wide_fwd", "adj": "mlp_wide_adj", "hadj": "prod_wide_nn"} if wl.cell == "resmlp" else \
+            fam = {"fwd": "mlp_wide_fwd", "adj": "mlp_wide_adj",
+                   "hadj": "mlp_back_wide" if back else "prod_wide_nn"} if wl.cell == "resmlp" else \
                 {"fwd": "cell_wide_fwd", "adj": "cell_wide_adj", "hadj": "prod_wide_nt"}
             key = fam.get(dom, "dw_bf16")
         elif small:
-            key = {"fwd": "step_small_fwd", "adj": "step_small_adj"}.get(dom, "dw_lds_f32")
+            key = {"fwd": "step_small_fwd", "adj": "step_small_adj"}.get(
+                dom, "dw_bf16" if wl.dtype == "bf16" else "dw_f32x3" if dw_x3 else "dw_lds_f32")
         else:
             key = {"fwd": "step_f32_fwd", "adj": "step_f32_adj"}.get(dom, "dw_f32_big")
         traffic = measured_traffic(wl.name, key)

@@ -89,6 +89,34 @@ def test_mlp_layer_work_reduces_to_one_width():
     assert f2["adj"] == (2 * 4 * 16 * 32 + 2 * 4 * 32 * 16 + 2 * 4 * 32 * 16) / 2
 
 
+def test_mlp_adjoint_launch_forms_one_product():
+    B, w, n = 8, 32, 5
+    f, b = bench.mlp_adjoint_launch([w] * (n + 1), B)
+    assert f == 2.0 * B * w * w
+    assert b == 4.0 * (w * w + (5 * (n - 1) + 3) / n * B * w + w / n)
+    assert bench.mlp_adjoint_launch([16, 32, 16], 4)[0] == (2 * 4 * 32 * 16 + 2 * 4 * 32 * 16) / 2
+
+
+def test_rules_of_the_split_fp32_kernels():
+    import synth
+    import paper_1806_01117_amd as amb
+
+    def spec(name, **kw):
+        return amb.ProblemSpec.from_workload(synth.get(name).with_(**kw))
+    big = spec("lstm_h4096_t20000")
+    assert bench.split_dw(big, [], 16) and not bench.split_dw(big, [("lds_gemm", 2)], 16)
+    small = spec("lstm_h512_t1000", batch=5, input=16, hidden=48)         # a gradient of 192 x 64
+    assert not bench.split_dw(small, [], 12) and bench.split_dw(small, [], 13)
+    assert bench.split_dw(spec("lstm_h512_t1000", batch=1), [], 1)         # 2048 x 768
+    assert not bench.split_dw(spec("mlp_widths_l2000"), [], 8)
+    assert not bench.split_dw(spec("lstm_h2048_bf16_t10000"), [], 64)
+    # which paths keep pre-activations for their adjoints
+    assert bench.keeps_steps(big, [], True) and not bench.keeps_steps(big, [("lds_gemm", 2)], True)
+    assert not bench.keeps_steps(big, [("kept_steps", 0)], True)
+    assert bench.keeps_steps(small, [], False) and bench.keeps_steps(spec("resmlp_w4096_l2000_bf16"), [], True)
+    assert not bench.keeps_steps(spec("mlp_widths_l2000"), [], False)
+
+
 def test_pmc_table_names_kernel_instances():
     from paper_1806_01117_amd.pmc_summary import _instance
     assert _instance("void ambptt::(anonymous namespace)::mlpv_gemm<3, 1, 4>(ambptt::MlpvArgs)") == "mlpv_gemm<3, 1, 4>"
