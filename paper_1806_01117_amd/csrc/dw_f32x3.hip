@@ -18,10 +18,11 @@
 // anyway: a thread sums its own rows, and the 8 threads of a column are added
 // in order.
 //
-// Bound: the matrix cores at the clock that the power limit leaves them (see
-// gemm_f32x3.hip).  The 4096-LSTM's window (16384 x 5120, 8192 rows, 8.2
-// TFLOP of bf16 products) takes 6.8 ms against 10.8-11.6 ms on fp32 MFMAs,
-// 1.21 PFLOP/s; 4096 x 1120 over 7200 rows 0.50 ms against 0.99; 4096 x 1280
+// Bound: the matrix cores, 63 % busy in the 4096-LSTM's window at the 1.8 GHz
+// that this load leaves of 2.4 (MFMAs alone on such operands run at 2.0 GHz);
+// its waves wait a quarter of the time.  That window (16384 x 5120, 8192 rows,
+// 8.2 TFLOP of bf16 products) takes 7.0 ms against 10.8-11.6 ms on fp32 MFMAs,
+// 1.17 PFLOP/s; 4096 x 1120 over 7200 rows 0.51 ms against 0.99; 4096 x 1280
 // over 1024 rows 77 us against 124; one fp32 residual MLP layer, 1040 x 1040
 // over 70 rows, 9.5 us against 14.0; 320 x 288 over 320 rows 21 us against 34.
 #include <hip/hip_runtime.h>
