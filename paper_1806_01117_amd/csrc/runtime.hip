@@ -2182,9 +2182,10 @@ static ambptt_status run_pass(ambptt_ctx* C, const void* x_seq, const void* W, c
   }
   if ((s = E.final_step(dh0, dc0)) != AMBPTT_OK) return s;
   const double t_enq = now_us();
+  // (the MLP of different widths scales each layer's mean by its own width)
   double scale = 1.0;
   if (p.loss == AMBPTT_LOSS_HALF_SQ_LAST) scale = 0.5;
-  else scale = 1.0 / ((double)p.batch * p.hidden);
+  else if (!L.mlpv) scale = 1.0 / ((double)p.batch * p.hidden);
   double* dloss = (double*)(C->ws + L.off_lossout);
   HIPCK(launch_loss_sum((const double*)(C->ws + L.off_loss), L.loss_slots, scale, dloss, C->cs));
   HIPCK(hipMemcpyAsync(C->host_loss, dloss, sizeof(double), hipMemcpyDeviceToHost, C->cs));

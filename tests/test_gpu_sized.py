@@ -99,6 +99,16 @@ def test_a_short_mlp_writes_its_gradients_and_nothing_else(n, widths):
                      wl, TOL_F32)
 
 
+@pytest.mark.parametrize("loss", ["mean_sq_all", "mean_last"])
+def test_mean_losses_of_different_widths(loss):
+    # each layer's mean is over its own B w_{l+1} values
+    wl = synth.get("mlp_widths_l2000").with_(n_steps=9, batch=20, hidden=128, widths=(64, 128, 32, 48), loss=loss)
+    host, dev = _case(wl)
+    a = run_gpu(wl, dev, fast_slots=3, slow_slots=9, interval_min=2)
+    assert_close_mlp(a, run_oracle(wl, *host), wl, TOL_F32)
+    assert_bitwise(a, run_gpu(wl, dev, fast_slots=10, slow_slots=0))
+
+
 def test_mlp_widths_refusals():
     import paper_1806_01117_amd as amb
     from paper_1806_01117_amd._lib import EINVAL, EUNSUPPORTED, AmbpttError
